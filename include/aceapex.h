@@ -179,7 +179,13 @@ int aceapex_decoder_stage_ms(aceapex_decoder* dec, float* ans_ms, float* parse_m
 /* 1 = record stage events on later decodes (five event records per window). */
 int aceapex_decoder_set_timing(aceapex_decoder* dec, int enable);
 
-/* Decoder options (schedule knobs; none changes a decoded byte).
+/* Decoder options (schedule knobs; none changes a decoded byte).  With every
+ * match-layer knob at its default the match layer follows each match to the
+ * literal bytes it comes from, without rounds; AX_OPT_BULK_ROUNDS,
+ * AX_OPT_FILL_ROUNDS, AX_OPT_FILL_TAIL, AX_OPT_TAIL_CHUNKS,
+ * AX_OPT_ROUND0_TILE, AX_OPT_TAIL_MODE and AX_OPT_JUMP_PASSES describe the
+ * level-synchronous schedule, which runs when one of them is set to another
+ * value than its default, and in the serial copy mode.
  *   AX_OPT_BULK_ROUNDS  number of level-synchronous match-layer rounds (one
  *     launch each, plain cached accesses) before the launches that finish the
  *     deeper tokens, in [1, 250] (default 4).  Until it is set, a decoder
@@ -224,9 +230,10 @@ enum { AX_OPT_TAIL_MODE = 7 };
  *     [1, 32] = at most k passes.  The final gather follows whatever entries the passes left, so
  *     the count changes timing only, never a byte. */
 enum { AX_OPT_JUMP_PASSES = 8 };
-/*   AX_OPT_RANGE_JUMP_TOKENS  range decodes of this decoder finish closures of
- *     at least this many matches by pointer jumping, smaller ones by the
- *     persistent launch (default 4096; 0 = always jump). */
+/*   AX_OPT_RANGE_JUMP_TOKENS  range decodes of this decoder that run the
+ *     level-synchronous schedule finish closures of at least this many matches
+ *     by pointer jumping, smaller ones by the persistent launch (default 4096;
+ *     0 = always jump). */
 enum { AX_OPT_RANGE_JUMP_TOKENS = 9 };
 int aceapex_decoder_set_option(aceapex_decoder* dec, int option, int64_t value);
 

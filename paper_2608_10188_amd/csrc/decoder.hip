@@ -13,22 +13,27 @@
 //            history tuples); literal runs are placed into an LDS tile that
 //            is written out with 16-byte stores; matches become tokens
 //            (src, dst, len).
-//   match layer: every token (src, dst, len) is written as a periodic fill
-//            out[dst+k] = out[src + k mod dist] (periodic-fill section).  The
-//            tokens whose destinations meet a token's source bytes form one
-//            contiguous index range (tokens are stored in output order), found
-//            once by binary search; a token is ready when those are done.
-//            k_round0 (a workgroup per block, fills gathered in an LDS tile of
-//            the block's chunks that receive match bytes) and k_round run
-//            level-synchronous rounds (the dependency levels of the paper's
-//            wavefront decoder) with plain cached accesses, the kernel
-//            boundary being the only synchronisation.  The last round
-//            marks its leftovers in a bitmap, which k_pcount / k_pscatter
-//            compact into an ascending list; k_tail then finishes that deep
-//            remainder in one persistent launch, waves taking 64-token chunks
-//            of the list from a ticket counter and publishing through
-//            agent-coherent stores, so a dependency hop costs a memory round
-//            trip rather than an L2 writeback.
+//   match layer: every token (src, dst, len) is a periodic fill
+//            out[dst+k] = out[src + k mod dist] (periodic-fill section).  Two
+//            schedules:
+//   - roots (the default): no token waits for another.  k_roots follows each
+//     piece of a match's source to the literal bytes it comes from, which are
+//     final after the parse; the bytes of long chains, and every byte of
+//     archives taken to be deep (k_mark), become entries of a jump array that
+//     k_sweep and k_finish resolve.
+//   - rounds (chosen by the schedule options, and for the serial ablation):
+//     the tokens whose destinations meet a token's source bytes form one
+//     contiguous index range (tokens are stored in output order), found once
+//     by binary search; a token is ready when those are done.  k_round0 (a
+//     workgroup per block, fills gathered in an LDS tile of the block's chunks
+//     that receive match bytes) and k_round run level-synchronous rounds (the
+//     dependency levels of the paper's wavefront decoder) with plain cached
+//     accesses, the kernel boundary being the only synchronisation.  The last
+//     round's leftovers are finished by pointer jumping over window positions
+//     (k_jmarklong ... k_jgather), or marked in a bitmap that k_pcount /
+//     k_pscatter compact into an ascending list for k_tail, one persistent
+//     launch whose waves take 64-token chunks from a ticket counter and publish
+//     through agent-coherent stores.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -55,6 +60,9 @@ __device__ inline AX_GLOBAL T* gp(T* p) {
 }
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef u32x4 u32x4_u __attribute__((aligned(1)));  // 16 bytes at any byte address (one dwordx4 load)
+typedef u32x4 u32x4_w __attribute__((aligned(4)));  // four words at any word address
+typedef uint32_t u32_u __attribute__((aligned(1)));
+typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
 
 constexpr uint32_t kMaxB = 16384;           // largest block the device path decodes
 constexpr uint32_t kParseThreads = 256;
@@ -410,21 +418,31 @@ __global__ __launch_bounds__(64) void k_ans(AnsArgs a) {
 
 // ---------------------------------------------------------------- k_parse --
 
+// What the match layer looks source positions up in (kRecs), one record per
+// 32 positions of a block: x = match coverage, y = token starts, z = the
+// window's tokens starting before these positions, w = the next 32 positions'
+// coverage, so one 16-byte load answers a lookup.  A block's records take the
+// first half of its own command slot, dead when its parse ends.
+__device__ inline AX_GLOBAL u32x4* block_recs(uint8_t* cmd, uint32_t slot_b, uint32_t item) {
+  return reinterpret_cast<AX_GLOBAL u32x4*>(gp(cmd + uint64_t(item) * slot_b));
+}
+
 struct ParseArgs {
   const JobDev* jobs;
   const WinBlock* wbl;
   uint32_t n_items;
   uint32_t n_tok;            // tokens in the window
   uint32_t slot_b;
-  const uint8_t *lit, *cmd, *off, *len;
+  const uint8_t* lit;
+  uint8_t* cmd;              // the commands; then the records (kRecs)
+  const uint8_t *off, *len;
   uint32_t off_cap, len_cap;
   const uint32_t* nsym;
   uint64_t* tok;             // 2 u64 per token: src, dst | (len-1) << 48
-  uint32_t* tblk;            // per token: its window block
+  uint32_t* tblk;            // per token: its window block (null: the match layer needs neither this nor done)
   uint8_t* done;             // per token: kPending until the match layer copies it
   DevStatus* st;
   int write_out;             // 0: tokens only (the token-index build), no output bytes
-  uint16_t* mcov;            // match coverage: per window position, set when a match writes it (16 per u16)
 };
 
 // History maps.  A command acts on the four-entry distance history as a map
@@ -451,7 +469,11 @@ __device__ inline uint64_t pick4(const uint64_t h[4], uint64_t j) {
 }
 
 struct ParseShared {
-  __attribute__((aligned(16))) uint8_t tile[kMaxB];
+  // the literal bytes of the 16-byte group a chunk leaves open, by chunk
+  // parity (a chunk reads its predecessor's while it may write its own)
+  u32x4 gcarry[2];
+  uint64_t covw[kMaxB / 64];      // match coverage of the block's output positions (kRecs)
+  uint64_t startw[kMaxB / 64];    // token starts among them (kRecs)
   uint64_t runbits[kMaxB / 64];   // starts of the chunk's literal runs, in the block's output positions
   uint16_t runpre[kMaxB / 64];    // run starts in earlier words
   uint16_t rundelta[kParseThreads];  // per run: output position - literal index
@@ -639,8 +661,8 @@ __device__ bool leb_values(Src src, uint32_t n, uint32_t* cursor, uint32_t count
   return true;
 }
 
-// Six waves per SIMD (at most 80 VGPRs), as many as the LDS allows.
-template <class O, bool kCovMap>
+// Six waves per SIMD (at most 80 VGPRs).
+template <class O, bool kRecs>
 __global__ __launch_bounds__(kParseThreads, 6) void k_parse(ParseArgs a) {
   __shared__ ParseShared sh;
   const uint32_t item = blockIdx.x, t = threadIdx.x;
@@ -662,6 +684,11 @@ __global__ __launch_bounds__(kParseThreads, 6) void k_parse(ParseArgs a) {
   if (t == 0)
     sh.bad = (n_lit > B || n_cmd > B || n_len > job_len_cap(J) || n_off > job_off_cap(J) ||
               tok_lo + tok_n > a.n_tok) ? 1 : 0;
+  if (kRecs && t < kMaxB / 64) sh.covw[t] = 0, sh.startw[t] = 0;
+  static_assert(kMaxB / 64 <= kParseThreads, "one map word per thread");
+  // the block's output bytes (contiguous); groups below `full` are whole
+  AX_GLOBAL uint8_t* const o = a.write_out ? O(J).at(bs) : nullptr;
+  const uint32_t full = blen & ~15u;
   // the first chunk's command bytes, loaded ahead of the staging barrier
   // (inside the slot whatever the count: kParseThreads <= slot_b)
   uint32_t cnext = cmd[t];
@@ -773,8 +800,11 @@ __global__ __launch_bounds__(kParseThreads, 6) void k_parse(ParseArgs a) {
         uint64_t* tk = a.tok + 2 * (tok_lo + gi);
         tk[0] = src;
         tk[1] = absdst | (uint64_t(len - 1) << 48);
-        a.tblk[tok_lo + gi] = item;
-        a.done[tok_lo + gi] = kPending;
+        if (a.tblk) {
+          a.tblk[tok_lo + gi] = item;
+          a.done[tok_lo + gi] = kPending;
+        }
+        if (kRecs) atomicOr(reinterpret_cast<uint32_t*>(sh.startw) + (cdst >> 5), 1u << (cdst & 31));
       } else {
         bad = true;
       }
@@ -799,15 +829,15 @@ __global__ __launch_bounds__(kParseThreads, 6) void k_parse(ParseArgs a) {
     __syncthreads();
     // place the chunk's literal bytes by aligned 16-byte output groups: each
     // literal run meeting a group supplies the 16 literal bytes lined up with
-    // the group under the group's byte mask, and the group is merged into the
-    // tile with one 16-byte read and write (bytes outside the runs keep their
-    // value)
+    // the group under the group's byte mask, and the group leaves with one
+    // 16-byte store (zeros where matches will be).  The group the chunk ends
+    // in is carried to the next chunk, which begins in it
     const uint32_t dend = dst + uint32_t(ptot & 0xFFFFFFFFu);
     for (uint32_t c = (dst >> 4) + t; 16 * c < dend; c += kParseThreads) {
       const uint32_t d0 = max(16 * c, dst), d1 = min(16 * c + 16, dend), w = d0 >> 6;
       int32_t r = int32_t(sh.runpre[w] + __popcll(sh.runbits[w] & (~0ull >> (63 - (d0 & 63))))) - 1;
       if (r < 0 || d0 >= sh.runend[r]) ++r;  // the run holding d0, else the next one
-      u32x4 val = {0, 0, 0, 0}, msk = {0, 0, 0, 0};
+      u32x4 val = {0, 0, 0, 0};
       uint32_t lit16 = 0;  // the group's literal bytes in this chunk
       for (; r < int32_t(n_runs) && sh.runbeg[r] < d1; ++r) {
         const uint32_t x0 = max(d0, uint32_t(sh.runbeg[r])), x1 = min(d1, uint32_t(sh.runend[r]));
@@ -825,20 +855,26 @@ __global__ __launch_bounds__(kParseThreads, 6) void k_parse(ParseArgs a) {
         const u32x4 bm = {__builtin_amdgcn_perm(0u, 0u, sel.x), __builtin_amdgcn_perm(0u, 0u, sel.y),
                           __builtin_amdgcn_perm(0u, 0u, sel.z), __builtin_amdgcn_perm(0u, 0u, sel.w)};
         val = (val & ~bm) | (e & bm);
-        msk |= bm;
         lit16 |= m16;
         if (sh.runend[r] >= d1) break;
       }
-      if (kCovMap) {  // match coverage of the group: its bytes in this chunk that no literal fills
+      const uint32_t par = (c0 / kParseThreads) & 1;
+      const bool head = d0 > 16 * c, open = d1 < 16 * c + 16 && d1 < blen;  // begun in / goes on in another chunk
+      if (kRecs) {  // match coverage of the group: its bytes in this chunk that no literal fills
         uint32_t m = ((1u << (d1 - 16 * c)) - 1u) & ~((1u << (d0 - 16 * c)) - 1u) & ~lit16;
-        const uint32_t par = (c0 / kParseThreads) & 1;
-        if (d0 > 16 * c) m |= sh.mcarry[par ^ 1];  // the group began in the previous chunk
-        if (d1 < 16 * c + 16 && d1 < blen) sh.mcarry[par] = m;  // it goes on in the next chunk
-        else a.mcov[uint64_t(item) * (a.slot_b / 16) + c] = uint16_t(m);
+        if (head) m |= sh.mcarry[par ^ 1];
+        if (open) sh.mcarry[par] = m;
+        else reinterpret_cast<uint16_t*>(sh.covw)[c] = uint16_t(m);
       }
-      if (msk.x | msk.y | msk.z | msk.w) {
-        u32x4& cell = *reinterpret_cast<u32x4*>(sh.tile + 16 * c);
-        cell = (cell & ~msk) | val;
+      if (head) val |= sh.gcarry[par ^ 1];
+      if (open) {
+        sh.gcarry[par] = val;
+      } else if (a.write_out) {
+        if (16 * c < full) {
+          *reinterpret_cast<AX_GLOBAL u32x4*>(o + 16 * c) = val;
+        } else {
+          for (uint32_t i = 16 * c; i < blen; ++i) o[i] = uint8_t(val[(i >> 2) & 3] >> (8 * (i & 3)));
+        }
       }
     }
     __syncthreads();
@@ -852,13 +888,17 @@ __global__ __launch_bounds__(kParseThreads, 6) void k_parse(ParseArgs a) {
     if (t == 0) report(a.st, AX_E_CORRUPT, b);
     return;
   }
-  if (!a.write_out) return;
-  // write the tile with 16-byte stores (match bytes are filled by the match layer)
-  AX_GLOBAL uint8_t* o = O(J).at(bs);  // the block's bytes are contiguous
-  const uint32_t full = blen & ~15u;
-  for (uint32_t k = 16 * t; k < full; k += 16 * kParseThreads)
-    *reinterpret_cast<AX_GLOBAL u32x4*>(o + k) = *reinterpret_cast<const u32x4*>(sh.tile + k);
-  for (uint32_t k = full + t; k < blen; k += kParseThreads) o[k] = sh.tile[k];
+  if (!kRecs) return;
+  // the records the match layer looks sources up in: two per thread
+  const uint64_t cw = sh.covw[t], sw = sh.startw[t];
+  uint64_t all;
+  const uint32_t pre = uint32_t(tok_lo) + uint32_t(block_excl_sum64(uint64_t(__popcll(sw)), &all, sh, 0));
+  if (t < B / 64) {
+    const uint32_t cn = t + 1 < B / 64 ? uint32_t(sh.covw[t + 1]) : 0u;
+    AX_GLOBAL u32x4* const r = block_recs(a.cmd, a.slot_b, item) + 2 * t;
+    r[0] = u32x4{uint32_t(cw), uint32_t(sw), pre, uint32_t(cw >> 32)};
+    r[1] = u32x4{uint32_t(cw >> 32), uint32_t(sw >> 32), pre + uint32_t(__popc(uint32_t(sw))), cn};
+  }
 }
 
 // ------------------------------------------------------------ match layer --
@@ -892,8 +932,7 @@ struct CopyArgs {
   uint32_t* J;                // pointer jumping: one entry per window position
   uint64_t* lmap;             // pointer jumping: leftover map
   uint32_t S;                 // position stride of a window block
-  const uint64_t* mcov;       // match coverage of the window positions (the parse writes it when round 0
-                              // is the only bulk round; null: round 0 finds every cover)
+  uint8_t* cmd;              // command slots holding the parse's records (null: round 0 finds every cover)
   uint32_t one_job;           // 1: the plan has one job, so every token's output is jobs[0]'s
 };
 
@@ -1177,16 +1216,15 @@ __device__ inline bool window_block(const WinBlock* wbl, uint32_t S, const WinBl
 __device__ inline bool sources_literal(const CopyArgs& a, const WinBlock& wb, uint32_t item, uint64_t bs, uint32_t B,
                                        uint64_t s0, uint64_t s1) {
   const uint32_t lb = __builtin_ctz(B);
-  const AX_GLOBAL uint64_t* const mc = gp(a.mcov);
   while (s0 < s1) {
     const uint64_t qb = s0 >> lb, e = min(s1, (qb + 1) << lb);
     uint32_t wq = item * a.S;
     if (qb == (bs >> lb) || window_block(a.wbl, a.S, wb, qb, wq)) {
-      const uint32_t p0 = wq + uint32_t(s0 & (B - 1)), p1 = p0 + uint32_t(e - s0);  // window positions
-      for (uint32_t w = p0 >> 6; w <= (p1 - 1) >> 6; ++w) {
-        const uint32_t lo = w == (p0 >> 6) ? (p0 & 63) : 0, hi = w == ((p1 - 1) >> 6) ? ((p1 - 1) & 63) : 63;
-        const uint64_t m = (~0ull >> (63 - hi)) & (~0ull << lo);
-        if (mc[w] & m) return false;
+      const AX_GLOBAL u32x4* const rec = block_recs(a.cmd, a.S, wq / a.S);
+      const uint32_t p0 = uint32_t(s0 & (B - 1)), p1 = p0 + uint32_t(e - s0);  // block positions
+      for (uint32_t w = p0 >> 5; w <= (p1 - 1) >> 5; ++w) {
+        const uint32_t lo = w == (p0 >> 5) ? (p0 & 31) : 0, hi = w == ((p1 - 1) >> 5) ? ((p1 - 1) & 31) : 31;
+        if (rec[w].x & (~0u >> (31 - hi)) & (~0u << lo)) return false;
       }
     }
     s0 = e;
@@ -2161,6 +2199,705 @@ __global__ __launch_bounds__(kCopyThreads) void k_jgather(JumpArgs a) {
   });
 }
 
+// ------------------------------------------------------ match layer: roots --
+//
+// The match layer of the default schedule.  Every output byte of a match
+// comes, over a chain of matches, from a literal byte (or from a byte of an
+// earlier window), and literal bytes are final once the parse is through.  So
+// a match needs no other match to be written first: k_roots follows each
+// piece of a match's source to the literals behind it and copies those, all
+// blocks at once.  A step of such a walk looks up one of the parse's records:
+// a position is either a literal, then the bytes up to the next match are
+// taken, or the byte of a match, found by its rank, and the walk goes on at
+// that match's source.  A step is two loads of 16 bytes at unrelated
+// addresses, the record and then either the bytes or the match: what bounds
+// the kernel is the latency of these two loads times a wave's longest walk,
+// and how many such gathers a compute unit serves (one address per cycle), so
+// both cases share one load instruction (separate loads, the bytes always
+// among them: 382 us for the 254 MB DNA archive's matches, this form 220 us).
+//
+// A walk ends after kRootSteps steps: its bytes are marked as pending in a
+// bitmap, each with the window position it was followed to (the jump array),
+// and k_sweep and k_finish resolve them.  Walking on instead keeps a block's
+// whole workgroup for one lane.  In blocks of archives taken to be deep nearly
+// every walk would end so, and all bytes are marked at once (k_mark).
+//
+// Against the rounds schedule (same data, whole match layer): 254 MB DNA
+// 512 -> 330 us, 80 MiB text 1632 -> 600 us, 64 KiB DNA 122 -> 23 us.
+//
+// A block's window position o of window block x is x * S + o, as for the
+// pointer-jumping remainder of the rounds schedule, whose jump array (kJRes
+// marks a final byte) and leftover map these kernels use.
+
+constexpr uint32_t kRootItem = 16;   // bytes per work item: one 16-byte source load
+// Steps before a walk's bytes are left pending (decode of 254 MB DNA / 32 MiB
+// reads with 3, 4, 6, 9 and 12 steps: 861 / 273, 816 / 265, 778 / 262, 765 /
+// 262, 792 / 279 us).
+constexpr uint32_t kRootSteps = 9;
+
+struct RootArgs {
+  const JobDev* jobs;
+  const WinBlock* wbl;
+  uint32_t n_items;
+  uint32_t n_tok;
+  uint32_t s_log2;        // log2 S
+  const uint64_t* tok;    // window tokens in (job, output) order
+  uint8_t* cmd;           // command slots: the blocks' records
+  uint32_t* J;            // jump array: one entry per window position
+  uint64_t* lmap;         // pending bytes, one bit per window position
+  DevStatus* st;
+  uint32_t first;         // k_roots: the window's first block that is not deep
+  uint32_t mark_log2;     // k_mark: log2 of the positions of a workgroup
+};
+
+// Where source positions of a window block's job lie in the window, and where
+// their bytes are.  find() is false for positions of no block of the window:
+// those are final (an earlier window wrote them) or, in a range decode, not
+// needed by anybody.
+struct RootDirect {  // the job's blocks are consecutive in the window
+  gbytes out;
+  uint64_t j0, n_bytes;
+  uint32_t span, base, lb, sl;
+  __device__ RootDirect(const RootArgs& a, const JobDev& J, const WinBlock& wb)
+      : out(gp(J.out)), n_bytes(J.n_bytes), lb(uint32_t(__builtin_ctz(J.B))), sl(a.s_log2) {
+    j0 = a.wbl[wb.first].b << lb;
+    span = wb.count << lb;  // at most 2^31
+    base = wb.first << sl;
+  }
+  __device__ bool find(uint64_t s, uint32_t& pos) const {
+    const uint64_t rel = s - j0;
+    if (rel >= span) return false;
+    const uint32_t r = uint32_t(rel);
+    pos = base + ((r >> lb) << sl) + (r & ((1u << lb) - 1u));
+    return true;
+  }
+  // where the byte of s is; wide: 16 bytes may be read from there
+  __device__ gbytes byte_at(uint64_t s, bool, uint32_t, bool& wide) const {
+    wide = s + kRootItem <= n_bytes;
+    return out + s;
+  }
+};
+struct RootMapped {  // a range decode: slot x of the scratch is window block x (a stale entry names another block)
+  gbytes out;
+  const AX_GLOBAL uint32_t* slot;
+  const WinBlock* wbl;
+  uint32_t n_items, lb, junk;
+  __device__ RootMapped(const RootArgs& a, const JobDev& J, const WinBlock&)
+      : out(gp(J.out)), slot(gp(J.slot)), wbl(a.wbl), n_items(a.n_items), lb(uint32_t(__builtin_ctz(J.B))), junk(J.junk) {}
+  __device__ bool find(uint64_t s, uint32_t& pos) const {
+    const uint32_t x = slot[s >> lb];
+    if (x >= n_items || wbl[x].b != s >> lb) return false;
+    pos = (x << lb) + uint32_t(s & ((1u << lb) - 1u));
+    return true;
+  }
+  // the scratch holds the junk block behind the window's: 16 bytes from any
+  // window position, and for other positions bytes nobody needs
+  __device__ gbytes byte_at(uint64_t, bool in, uint32_t pos, bool& wide) const {
+    wide = true;
+    return out + (in ? uint64_t(pos) : uint64_t(junk) << lb);
+  }
+};
+template <class O> struct RootWin;
+template <> struct RootWin<OutDirect> { typedef RootDirect type; };
+template <> struct RootWin<OutMapped> { typedef RootMapped type; };
+
+// Inclusive wave scan of a u32 (maximum).
+__device__ inline uint32_t wave_incl_max32(uint32_t x) {
+  x = max(x, dpp_move<kDppRowShr + 1, 0xF>(0, x));
+  x = max(x, dpp_move<kDppRowShr + 2, 0xF>(0, x));
+  x = max(x, dpp_move<kDppRowShr + 4, 0xF>(0, x));
+  x = max(x, dpp_move<kDppRowShr + 8, 0xF>(0, x));
+  x = max(x, dpp_move<kDppRowBcast15, 0xA>(0, x));
+  x = max(x, dpp_move<kDppRowBcast31, 0xC>(0, x));
+  return x;
+}
+
+// Sixteen bytes as two words, byte 0 lowest.
+struct B16 {
+  uint64_t lo, hi;
+};
+__device__ inline B16 b16_low(B16 v, uint32_t m) {  // the first m <= 16 bytes
+  if (m < 8) return B16{v.lo & ((1ull << (8 * m)) - 1), 0};
+  return B16{v.lo, m < 16 ? v.hi & ((1ull << (8 * (m - 8))) - 1) : v.hi};
+}
+__device__ inline B16 b16_up(B16 v, uint32_t n) {  // moved up by n < 16 bytes
+  if (n >= 8) return B16{0, v.lo << (8 * (n - 8))};
+  return B16{v.lo << (8 * n), n ? (v.hi << (8 * n)) | (v.lo >> (64 - 8 * n)) : v.hi};
+}
+
+// One item's walk: bytes [0, kend) of the item come from archive positions
+// src0...; k of them are in acc.  s is where byte k's source was followed to,
+// standing for run bytes.  A source inside a self-overlapping match repeats
+// with its period: once a period of it is taken the rest is repeated from acc
+// (rep: period | first byte not taken yet << 8 | end << 16).
+struct Walk {
+  uint64_t src0, s, next_s;  // next_s, next_run: where the bytes after this run go on (run 0: at src0 + k)
+  uint32_t k, kend, run, next_run, rep;
+  B16 acc;
+  __device__ void go_on() {
+    if (next_run) s = next_s, run = next_run;
+    else s = src0 + k, run = kend - k;
+    next_run = 0;
+  }
+};
+
+// One step; false once the item is complete.
+template <class W>
+__device__ inline bool walk_step(Walk& x, const W& win, const RootArgs& a, uint32_t B) {
+  uint32_t pos = 0, r, u = 0;
+  const bool in = win.find(x.s, pos);
+  if (in) {
+    const uint32_t off = pos & ((1u << a.s_log2) - 1u), bit = off & 31u;
+    const u32x4 q = block_recs(a.cmd, 1u << a.s_log2, pos >> a.s_log2)[off >> 5];
+    const uint64_t cov = ((uint64_t(q.w) << 32) | q.x) >> bit;  // at least 33 positions: more than an item
+    r = cov ? uint32_t(__builtin_ctzll(cov)) : 64u;
+    r = min(r, B - off);
+    u = q.z + uint32_t(__popc(q.y & (~0u >> (31 - bit)))) - 1;
+  } else {  // final bytes, up to the end of their block
+    r = B - uint32_t(x.s & (B - 1));
+  }
+  bool wide;
+  const gbytes from = win.byte_at(x.s, in, pos, wide);
+  const gbytes p = r ? from : reinterpret_cast<gbytes>(gp(const_cast<uint64_t*>(a.tok)) + 2 * uint64_t(u));
+  u32x4 v = {0, 0, 0, 0};
+  const uint32_t m = min(r, x.run);
+  if (r == 0 || wide) {
+    v = *reinterpret_cast<const AX_GLOBAL u32x4_u*>(p);
+  } else {  // the output's last bytes
+    for (uint32_t i = 0; i < m; ++i) v[(i >> 2) & 3] |= uint32_t(p[i]) << (8 * (i & 3));
+  }
+  const B16 b = {uint64_t(v.x) | (uint64_t(v.y) << 32), uint64_t(v.z) | (uint64_t(v.w) << 32)};
+  if (r) {
+    const B16 up = b16_up(b16_low(b, m), x.k);
+    x.acc.lo |= up.lo, x.acc.hi |= up.hi;
+    x.k += m;
+    if (x.rep && x.k >= ((x.rep >> 8) & 0xFF)) {
+      const uint32_t pe = x.rep >> 16;
+      for (uint32_t span = x.rep & 0xFF; x.k < pe; span *= 2) {
+        // bytes [k, k + span) repeat those span before them
+        const uint32_t e = min(pe, x.k + span);
+        const B16 up = b16_up(x.acc, span), t = b16_low(up, e), below = b16_low(up, x.k);
+        x.acc.lo |= t.lo ^ below.lo, x.acc.hi |= t.hi ^ below.hi;
+        x.k = e;
+      }
+      x.rep = 0;
+      x.run = x.next_run = 0;
+    } else {
+      x.s += m, x.run -= m;
+    }
+    if (x.run == 0) x.go_on();
+    return x.k < x.kend;
+  }
+  const uint64_t us = b.lo, ud = b.hi & ((1ull << 48) - 1), dist = ud - us;
+  const uint32_t ulen = uint32_t(b.hi >> 48) + 1;
+  const uint32_t per = dist < ulen ? uint32_t(dist) : ulen;
+  uint32_t o = uint32_t(x.s - ud);
+  const uint32_t all = min(x.run, ulen - o);
+  if (all > per && !x.rep) x.rep = per | ((x.k + per) << 8) | ((x.k + all) << 16);
+  if (o >= per) o %= per;
+  const uint32_t run = min(all, per - o);
+  if (run < x.run) x.next_s = x.s + run, x.next_run = x.run - run;
+  x.run = run;
+  x.s = us + o;
+  return true;
+}
+
+// Jump-array entries of an item's bytes [k, kend), je = entry of its byte 0.
+template <class W>
+__device__ inline void mark_item(const Walk& x, const W& win, AX_GLOBAL uint32_t* je) {
+  const uint64_t s2 = x.src0 + x.k + x.run;  // the source of the bytes after this run
+  const uint32_t n2 = x.kend - x.k - x.run;
+  uint32_t pa = 0, pb = 0, pz = 0;
+  bool plain = win.find(x.s, pa) && win.find(x.s + x.run - 1, pz) && pz == pa + x.run - 1;
+  if (n2) plain = plain && win.find(s2, pb) && win.find(s2 + n2 - 1, pz) && pz == pb + n2 - 1;
+  if (plain) {  // both runs are consecutive window positions
+    const uint32_t cut = x.k + x.run, ea = pa - x.k, eb = pb - cut;
+#pragma unroll
+    for (uint32_t g = 0; g < kRootItem; g += 4) {
+      const u32x4 e = {(g < cut ? ea : eb) + g, (g + 1 < cut ? ea : eb) + g + 1, (g + 2 < cut ? ea : eb) + g + 2,
+                       (g + 3 < cut ? ea : eb) + g + 3};
+      if (x.k <= g && g + 4 <= x.kend) {
+        *reinterpret_cast<AX_GLOBAL u32x4_w*>(je + g) = e;
+      } else {
+#pragma unroll
+        for (uint32_t q = 0; q < 4; ++q)
+          if (g + q >= x.k && g + q < x.kend) je[g + q] = e[q];
+      }
+    }
+    return;
+  }
+  for (uint32_t j = x.k; j < x.kend; ++j) {
+    const uint64_t sp = j < x.k + x.run ? x.s + (j - x.k) : x.src0 + j;
+    uint32_t p = 0;
+    bool wide;
+    const bool in = win.find(sp, p);
+    je[j] = in ? p : kJRes | *win.byte_at(sp, false, 0, wide);
+  }
+}
+
+// The first m (1..16) bytes of v into the zero-filled tile at byte at: word
+// ORs, so items that share a word need no order.
+__device__ inline void tile_or(uint32_t* tile, uint32_t at, B16 v) {
+  // bytes moved up by at mod 4: selector 4 + i - shift picks from the word and the one before
+  const uint32_t sel = 0x07060504u - (at & 3) * 0x01010101u;
+  const uint32_t v0 = uint32_t(v.lo), v1 = uint32_t(v.lo >> 32), v2 = uint32_t(v.hi), v3 = uint32_t(v.hi >> 32);
+  uint32_t* const t = tile + (at >> 2);
+  const uint32_t w0 = __builtin_amdgcn_perm(v0, 0u, sel), w1 = __builtin_amdgcn_perm(v1, v0, sel),
+                 w2 = __builtin_amdgcn_perm(v2, v1, sel), w3 = __builtin_amdgcn_perm(v3, v2, sel),
+                 w4 = __builtin_amdgcn_perm(0u, v3, sel);
+  if (w0) atomicOr(t, w0);
+  if (w1) atomicOr(t + 1, w1);
+  if (w2) atomicOr(t + 2, w2);
+  if (w3) atomicOr(t + 3, w3);
+  if (w4) atomicOr(t + 4, w4);
+}
+
+// One workgroup per window block.  A token's first min(len, dist) bytes are
+// cut into items of kRootItem bytes, laid end to end over the wave's lanes;
+// the rest of a self-overlapping token repeats them (periodic fill) from the
+// tile.  The tile starts zeroed and the parse left zeros where matches go, so
+// a 16-byte chunk of the block is finished by OR-ing the tile into it, and
+// chunks without match bytes are not touched.
+template <class O>
+__global__ __launch_bounds__(kCopyThreads, 8) void k_roots(RootArgs a) {
+  __shared__ __attribute__((aligned(16))) uint32_t tile[kMaxB / 4 + 4];  // the last item's fifth word
+  __shared__ uint64_t row[kMaxB / 64];                                   // the block's pending bytes
+  __shared__ uint32_t heads[kCopyThreads];                               // per wave: tokens starting at an item
+  const uint32_t lane = lane_id(), item = a.first + xcd_item(blockIdx.x, gridDim.x);
+  const WinBlock wb = a.wbl[item];
+  const JobDev& J = a.jobs[wb.job];
+  const typename RootWin<O>::type win(a, J, wb);
+  const uint32_t B = J.B, sw = 1u << (a.s_log2 - 6);
+  const uint64_t bs = wb.b * B;
+  const gbytes ob = O(J).at(bs);
+  const uint32_t blen = uint32_t(min<uint64_t>(B, J.n_bytes - bs));
+  const uint32_t t1 = item + 1 < a.n_items ? a.wbl[item + 1].tok : a.n_tok;
+  const AX_GLOBAL uint64_t* const tok = gp(a.tok);
+  AX_GLOBAL uint32_t* const jarr = gp(a.J);
+  uint8_t* const tile8 = reinterpret_cast<uint8_t*>(tile);
+  uint32_t* const row32 = reinterpret_cast<uint32_t*>(row);
+  uint32_t* const hd = heads + (threadIdx.x & ~63u);
+  // the status is checked once the block's own loads are in flight
+  if (__hip_atomic_load(&a.st->err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) return;
+  for (uint32_t k = threadIdx.x; k < kMaxB / 16; k += kCopyThreads)
+    *reinterpret_cast<u32x4*>(tile + 4 * k) = u32x4{0, 0, 0, 0};
+  if (threadIdx.x < kMaxB / 64) row[threadIdx.x] = 0;
+  __syncthreads();
+  bool wpend = false;  // this wave left bytes pending
+  const uint32_t jblk = item << a.s_log2;  // window position of the block's first byte
+  for (uint32_t base = wb.tok + (threadIdx.x & ~63u); base < t1; base += kCopyThreads) {
+    const uint32_t t = base + lane;
+    const bool have = t < t1;
+    uint64_t tsrc = 0;
+    uint32_t trel = 0, tlen = 0, tn = 0;
+    if (have) {
+      tsrc = tok[2 * uint64_t(t)];
+      const uint64_t w = tok[2 * uint64_t(t) + 1], dst = w & ((1ull << 48) - 1);
+      tlen = uint32_t(w >> 48) + 1;
+      trel = uint32_t(dst - bs);
+      const uint64_t dist = dst - tsrc;
+      tn = dist < tlen ? uint32_t(dist) : tlen;
+    }
+    const uint32_t mine = (tn + kRootItem - 1) / kRootItem;
+    const uint32_t incl = wave_incl_sum32(mine), start = incl - mine;
+    const uint32_t total = __builtin_amdgcn_readlane(incl, 63);
+    for (uint32_t i0 = 0; i0 < total; i0 += 64) {
+      // the token of item i0 + lane: the last one starting at or before it
+      hd[lane] = 0;
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      if (have && start >= i0 && start < i0 + 64) hd[start - i0] = lane;
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      const uint32_t first = uint32_t(__popcll(__ballot(have && start <= i0))) - 1;
+      const int l = int(max(first, wave_incl_max32(hd[lane])));
+      const uint32_t sub = i0 + lane - __shfl(start, l, 64);
+      const uint32_t at = __shfl(trel, l, 64) + kRootItem * sub;  // block position
+      Walk x;
+      x.src0 = __shfl((unsigned long long)tsrc, l, 64) + kRootItem * sub;
+      x.s = x.src0;
+      x.kend = min(kRootItem, __shfl(trel, l, 64) + __shfl(tn, l, 64) - at);
+      x.k = 0, x.run = x.kend, x.next_run = x.rep = 0, x.acc = B16{0, 0};
+      bool act = i0 + lane < total;
+      const uint32_t n0 = uint32_t(__popcll(__ballot(act)));
+      bool deep = false;
+      for (uint32_t step = 0; step < kRootSteps; ++step) {
+        const uint32_t left = uint32_t(__popcll(__ballot(act)));
+        if (!left) break;
+        // most walks of a large wave still going: a deep archive
+        deep = n0 >= 16 && step == 2 && 4 * left > 3 * n0;
+        if (deep) break;
+        if (act) act = walk_step(x, win, a, B);
+      }
+      if (i0 + lane < total && x.k) tile_or(tile, at, x.acc);
+      if (__ballot(act)) {  // items left walking: their bytes are pending, named by where the walk stands
+        wpend = true;
+        if (act) {
+          mark_item(x, win, jarr + jblk + at);
+          const uint64_t m = uint64_t(((1u << x.kend) - 1u) & ~((1u << x.k) - 1u)) << (at & 31);
+          atomicOr(&row32[at >> 5], uint32_t(m));
+          if (m >> 32) atomicOr(&row32[(at >> 5) + 1], uint32_t(m >> 32));
+        }
+      }
+    }
+    // self-overlapping tokens: byte j >= dist repeats byte j mod dist of the token
+    uint64_t rep = __ballot(tlen > tn);
+    if (rep) {
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+    }
+    while (rep) {
+      const int l = __builtin_ctzll(rep);
+      rep &= rep - 1;
+      const uint32_t d0 = __builtin_amdgcn_readlane(trel, l), n = __builtin_amdgcn_readlane(tlen, l),
+                     per = __builtin_amdgcn_readlane(tn, l);
+      const uint32_t jstep = 64 % per;
+      uint32_t j = lane % per;
+      for (uint32_t k = per + lane; k < n; k += 64) {
+        if (wpend && ((row32[(d0 + j) >> 5] >> ((d0 + j) & 31)) & 1)) {
+          jarr[jblk + d0 + k] = jblk + d0 + j;
+          atomicOr(&row32[(d0 + k) >> 5], 1u << ((d0 + k) & 31));
+        } else {
+          tile8[d0 + k] = tile8[d0 + j];
+        }
+        j += jstep;
+        if (j >= per) j -= per;
+      }
+    }
+  }
+  const int any = __syncthreads_or(int(wpend));
+  const uint32_t full = blen / 16, nchunk = (blen + 15) / 16;
+  for (uint32_t c = threadIdx.x; c < nchunk; c += kCopyThreads) {
+    const u32x4 x = *reinterpret_cast<const u32x4*>(tile + 4 * c);
+    if (!(x.x | x.y | x.z | x.w)) continue;
+    if (c < full) {
+      AX_GLOBAL u32x4* const p = reinterpret_cast<AX_GLOBAL u32x4*>(ob + 16 * c);
+      *p = *p | x;
+    } else {
+      for (uint32_t i = 16 * c; i < blen; ++i) ob[i] |= tile8[i];
+    }
+  }
+  if (threadIdx.x < sw) gp(a.lmap)[uint64_t(item) * sw + threadIdx.x] = threadIdx.x < kMaxB / 64 ? row[threadIdx.x] : 0ull;
+  if (any && threadIdx.x == 0) a.st->n_pending = 1;
+}
+
+// log2 of the positions a workgroup of k_mark takes: small in small windows,
+// where a workgroup's chain of loads is what counts (text 1 MB: 94 -> 91 us
+// for the decode with 1024 instead of 4096), large in others (text 80 MiB:
+// 783 -> 764 us with 4096)
+constexpr uint32_t kMarkSmallLog2 = 10, kMarkLog2 = 12;
+
+// Blocks of deep archives: walks would not end in a few steps, so every byte
+// gets its jump-array entry at once, four consecutive positions a lane (the
+// record shared by eight lanes, one 16-byte store each): a match byte names
+// its source, any other holds its value.  The bitmap has every byte of the
+// block.
+template <class O>
+__global__ __launch_bounds__(kCopyThreads) void k_mark(RootArgs a) {
+  const uint32_t part = xcd_item(blockIdx.x, gridDim.x), lp = a.s_log2 - a.mark_log2;  // parts per block: 2^lp
+  const uint32_t item = part >> lp, p0 = (part & ((1u << lp) - 1u)) << a.mark_log2;
+  const WinBlock wb = a.wbl[item];
+  const JobDev& J = a.jobs[wb.job];
+  const typename RootWin<O>::type win(a, J, wb);
+  const uint32_t B = J.B, sw = 1u << (a.s_log2 - 6);
+  const uint64_t bs = wb.b * B;
+  const gbytes ob = O(J).at(bs);
+  const uint32_t blen = uint32_t(min<uint64_t>(B, J.n_bytes - bs));
+  const AX_GLOBAL u64x2* const tok = reinterpret_cast<const AX_GLOBAL u64x2*>(gp(a.tok));
+  const AX_GLOBAL u32x4* const rec = block_recs(a.cmd, 1u << a.s_log2, item);
+  AX_GLOBAL uint32_t* const je = gp(a.J) + (uint64_t(item) << a.s_log2);
+  if (__hip_atomic_load(&a.st->err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) return;
+  for (uint32_t p = p0 + 4 * threadIdx.x; p < min(blen, p0 + (1u << a.mark_log2)); p += 4 * kCopyThreads) {
+    const u32x4 q = rec[p >> 5];
+    const uint32_t bit = p & 31u, cov = (q.x >> bit) & 0xFu;
+    uint32_t lit = 0;
+    if (cov != 0xFu) {
+      if (p + 4 <= blen) lit = *reinterpret_cast<const AX_GLOBAL uint32_t*>(ob + p);
+      else
+        for (uint32_t e = 0; p + e < blen; ++e) lit |= uint32_t(ob[p + e]) << (8 * e);
+    }
+    uint32_t u = q.z + uint32_t(__popc(q.y & (~0u >> (31 - bit)))) - 1;  // the match of byte 0, if it has one
+    const uint32_t starts = q.y >> bit;
+    u64x2 t = {0, 0};
+    if (cov & 1u) t = tok[u];
+    u32x4 v;
+#pragma unroll
+    for (uint32_t e = 0; e < 4; ++e) {
+      if (e && ((starts >> e) & 1u)) t = tok[++u];
+      uint32_t x = kJRes | ((lit >> (8 * e)) & 0xFFu);
+      if ((cov >> e) & 1u) {
+        const uint64_t ud = t.y & ((1ull << 48) - 1), dist = ud - t.x;
+        uint32_t o = uint32_t(bs + p + e - ud);
+        if (o >= dist) o %= uint32_t(dist);  // o < 2^16
+        uint32_t pos = 0;
+        const uint64_t s = t.x + o;
+        if (win.find(s, pos)) {
+          x = pos;
+        } else {
+          bool wide;
+          x = kJRes | *win.byte_at(s, false, 0, wide);
+        }
+      }
+      v[e] = x;
+    }
+    *reinterpret_cast<AX_GLOBAL u32x4*>(je + p) = v;
+  }
+  if (threadIdx.x < (1u << (a.mark_log2 - 6))) {
+    const uint32_t w = p0 + 64 * threadIdx.x;
+    gp(a.lmap)[uint64_t(item) * sw + (w >> 6)] = w + 64 <= blen ? ~0ull : w < blen ? (1ull << (blen - w)) - 1 : 0ull;
+  }
+  if (part == 0 && threadIdx.x == 0) a.st->n_pending = 1;
+}
+
+// ---- pending bytes: sweep and finish
+//
+// The blocks are cut into eight runs, one per XCD (workgroup g of a launch
+// goes to XCD g mod 8, whose L2 then holds the run's entries).
+// k_sweep walks each run's pending bytes in ascending order, following a
+// byte's entry to the first byte before the run or to a final byte, and
+// writes what it found back (a pass of pointer jumping reads and writes every
+// entry and only triples its reach: 80 MiB of text took five, 944 us, where
+// the sweep takes 243 us).  Entries name lower positions, so a walk soon
+// meets bytes that were swept before and carry their own walk's end: only
+// the bytes in flight are followed hop by hop, whatever the chain's length.
+// (Stale entries, from another compute unit's cache, name the same value and
+// only cost hops.)  After it, an entry holds its value or names a byte of an
+// earlier run; k_finish writes the bytes, following those.
+constexpr uint32_t kXcds = 8;
+constexpr uint32_t kSweepSlots = 4;    // bytes a lane follows at a time
+constexpr uint32_t kSweepRows = 8;     // map words a wave follows at a time where every byte has an entry
+constexpr uint32_t kSweepChunk = 8;    // consecutive map words a wave takes at a time
+constexpr uint32_t kSweepGrid = 2048;  // workgroups of a sweep or finish launch
+constexpr uint32_t kFinishWords = 8;   // map words a wave of k_finish has in flight
+constexpr uint32_t kFinishLimit = 1u << 24;  // hops k_finish follows before it reports a device error
+
+struct SweepArgs {
+  uint32_t s_log2;
+  uint32_t* J;
+  const uint64_t* lmap;
+  const JobDev* jobs;
+  const WinBlock* wbl;
+  uint32_t one_job;        // 1: the plan has one job, so window positions are contiguous in its output
+  uint8_t* const* ibase;   // else per window block: where its output bytes start
+  DevStatus* st;
+  uint32_t b0, b1;         // the blocks of this launch
+  uint32_t settled;        // k_finish: the bytes of the blocks before b0 are final
+};
+
+// Where the bytes of window positions are.
+struct PosOut {
+  gbytes lin;  // window position 0's byte, or null
+  uint8_t* const* ibase;
+  uint32_t sl;
+  __device__ explicit PosOut(const SweepArgs& a) : lin(nullptr), ibase(a.ibase), sl(a.s_log2) {
+    if (a.one_job) lin = gp(a.jobs->out) + (a.jobs->slot ? 0 : a.wbl->b << sl);
+  }
+  __device__ gbytes at(uint32_t v) const { return lin ? lin + v : gp(ibase[v >> sl]) + (v & ((1u << sl) - 1u)); }
+};
+
+// A wave's nonzero map words of 64: their indices and bits, in order.
+struct WordQueue {
+  uint64_t bits[64];
+  uint32_t g[64];
+};
+
+// The map words [w0, w0 + n), `waves` waves taking kSweepChunk words in turn:
+// step i of wave `wave` reads its next 64 words (64 / kSweepChunk chunks).
+__device__ inline uint32_t queue_words(const uint64_t* lmap, uint64_t w0, uint64_t n, uint64_t wave, uint64_t waves,
+                                       uint64_t i, WordQueue& q) {
+  const uint32_t lane = lane_id();
+  const uint64_t m = ((i * (64 / kSweepChunk) + lane / kSweepChunk) * waves + wave) * kSweepChunk + lane % kSweepChunk;
+  const uint64_t mw = m < n ? gp(lmap)[w0 + m] : 0ull;
+  const uint64_t nz = __ballot(mw != 0);
+  if (mw) {
+    const uint32_t at = lanes_below(nz);
+    q.bits[at] = mw;
+    q.g[at] = uint32_t(w0 + m);
+  }
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  return uint32_t(__popcll(nz));
+}
+
+// kAll: every byte of the blocks has an entry (k_mark), so a hop is one load.
+template <bool kAll>
+__global__ __launch_bounds__(kCopyThreads) void k_sweep(SweepArgs a) {
+  __shared__ WordQueue queues[kCopyThreads / 64];
+  if (a.st->n_pending == 0 || __hip_atomic_load(&a.st->err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) return;
+  const uint32_t lane = lane_id(), g = blockIdx.x / kXcds;
+  const uint32_t run = blockIdx.x % kXcds, runs = kXcds;
+  const uint64_t nb = a.b1 - a.b0;
+  const uint32_t b0 = a.b0 + uint32_t(nb * run / runs), b1 = a.b0 + uint32_t(nb * (run + 1) / runs);
+  const uint32_t lo = b0 << a.s_log2, wl = a.s_log2 - 6;
+  AX_GLOBAL uint32_t* const J = gp(a.J);
+  const AX_GLOBAL uint64_t* const lm = gp(a.lmap);
+  WordQueue& q = queues[threadIdx.x >> 6];
+  const PosOut po(a);
+  const uint64_t wave = uint64_t(g) * (kCopyThreads / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint64_t waves = uint64_t(gridDim.x / kXcds) * (kCopyThreads / 64);
+  const uint64_t n = uint64_t(b1 - b0) << wl;
+  for (uint64_t i = 0; i * 64 * waves < n; ++i) {
+    const uint32_t cnt = queue_words(a.lmap, uint64_t(b0) << wl, n, wave, waves, i, q);
+    if (kAll) {  // word by word: the bytes of a group of words leave as whole rows
+      for (uint32_t c = 0; c < cnt; c += kSweepRows) {
+        uint32_t v[kSweepRows], was[kSweepRows];
+        bool in[kSweepRows];
+#pragma unroll
+        for (uint32_t u = 0; u < kSweepRows; ++u) {
+          in[u] = c + u < cnt && ((q.bits[c + u < cnt ? c + u : 0] >> lane) & 1);
+          v[u] = in[u] ? J[q.g[c + u] * 64 + lane] : kJRes;
+          was[u] = v[u];
+        }
+        for (;;) {
+          bool more = false;
+#pragma unroll
+          for (uint32_t u = 0; u < kSweepRows; ++u)
+            if (!(v[u] & kJRes) && v[u] >= lo) v[u] = J[v[u]];
+#pragma unroll
+          for (uint32_t u = 0; u < kSweepRows; ++u) more |= !(v[u] & kJRes) && v[u] >= lo;
+          if (!__ballot(more)) break;
+        }
+#pragma unroll
+        for (uint32_t u = 0; u < kSweepRows; ++u)
+          if (v[u] != was[u]) J[q.g[c + u] * 64 + lane] = v[u];
+      }
+      continue;
+    }
+    // every lane follows its bit of the queue's words, kSweepSlots words at a
+    // time, each slot going on to its next word when its byte is done
+    uint32_t p[kSweepSlots], v[kSweepSlots], nx[kSweepSlots];  // byte (or none), where its walk is, next word
+#pragma unroll
+    for (uint32_t u = 0; u < kSweepSlots; ++u) p[u] = ~0u, v[u] = 0, nx[u] = u;
+    for (;;) {
+      bool busy = false;
+#pragma unroll
+      for (uint32_t u = 0; u < kSweepSlots; ++u) {
+        if (p[u] == ~0u && nx[u] < cnt) {
+          if ((q.bits[nx[u]] >> lane) & 1) p[u] = v[u] = q.g[nx[u]] * 64 + lane;
+          nx[u] += kSweepSlots;
+        }
+        busy |= p[u] != ~0u || nx[u] < cnt;
+      }
+      if (!__ballot(busy)) break;
+      uint32_t jn[kSweepSlots];
+      uint64_t w[kSweepSlots];
+#pragma unroll
+      for (uint32_t u = 0; u < kSweepSlots; ++u) {
+        jn[u] = kJRes, w[u] = 0;
+        if (p[u] != ~0u) w[u] = lm[v[u] >> 6], jn[u] = J[v[u]];
+      }
+#pragma unroll
+      for (uint32_t u = 0; u < kSweepSlots; ++u) {
+        if (p[u] == ~0u) continue;
+        const bool pend = (w[u] >> (v[u] & 63)) & 1;
+        v[u] = pend ? jn[u] : kJRes | *po.at(v[u]);
+        if ((v[u] & kJRes) || v[u] < lo) {
+          J[p[u]] = v[u];
+          p[u] = ~0u;
+        }
+      }
+    }
+  }
+}
+
+// The pending bytes of blocks [b0, b1), four consecutive positions a lane: an
+// entry holds the value or names an earlier byte.  With the blocks before b0
+// settled (launches in order) such a byte is read from the output; else the
+// entries are followed to the value, over at most one entry per run.
+template <bool kAll>
+__global__ __launch_bounds__(kCopyThreads) void k_finish(SweepArgs a) {
+  __shared__ WordQueue queues[kCopyThreads / 64];
+  if (a.st->n_pending == 0 || __hip_atomic_load(&a.st->err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) return;
+  const uint32_t lane = lane_id(), wl = a.s_log2 - 6, lo = a.settled ? a.b0 << a.s_log2 : 0u;
+  const AX_GLOBAL uint32_t* const J = gp(a.J);
+  const AX_GLOBAL uint64_t* const lm = gp(a.lmap);
+  WordQueue& q = queues[threadIdx.x >> 6];
+  const PosOut po(a);
+  const uint64_t wave = uint64_t(blockIdx.x) * (kCopyThreads / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint64_t waves = uint64_t(gridDim.x) * (kCopyThreads / 64);
+  const uint64_t n = uint64_t(a.b1 - a.b0) << wl;
+  const uint32_t sub = lane >> 4, q4 = 4 * (lane & 15u);
+  for (uint64_t i = 0; i * 64 * waves < n; ++i) {
+    const uint32_t cnt = queue_words(a.lmap, uint64_t(a.b0) << wl, n, wave, waves, i, q);
+    for (uint32_t c = 0; c < cnt; c += kFinishWords) {
+      constexpr uint32_t kRows = kFinishWords / 4;  // a lane's groups: word c + 4 h + lane / 16
+      uint32_t bits[kRows], p[kRows];
+      u32x4 x[kRows];
+#pragma unroll
+      for (uint32_t h = 0; h < kRows; ++h) {
+        const uint32_t wi = c + 4 * h + sub;
+        bits[h] = wi < cnt ? uint32_t(q.bits[wi] >> q4) & 0xFu : 0u;
+        p[h] = (wi < cnt ? q.g[wi] * 64 : 0u) + q4;
+        x[h] = u32x4{kJRes, kJRes, kJRes, kJRes};
+        if (bits[h]) x[h] = *reinterpret_cast<const AX_GLOBAL u32x4*>(J + p[h]);
+      }
+#pragma unroll
+      for (uint32_t h = 0; h < kRows; ++h)
+#pragma unroll
+        for (uint32_t e = 0; e < 4; ++e)
+          if (!((bits[h] >> e) & 1)) x[h][e] = kJRes;
+      for (uint32_t hop = 0;; ++hop) {  // to the value, or to a settled byte
+        bool more = false;
+#pragma unroll
+        for (uint32_t h = 0; h < kRows; ++h)
+#pragma unroll
+          for (uint32_t e = 0; e < 4; ++e) more |= !(x[h][e] & kJRes) && x[h][e] >= lo;
+        if (!__ballot(more)) break;
+        if (hop >= kFinishLimit) {
+          if (lane == 0) report(a.st, AX_E_DEVICE, ~0ull);
+          return;
+        }
+        uint64_t w[kRows][4];
+        uint32_t jn[kRows][4];
+#pragma unroll
+        for (uint32_t h = 0; h < kRows; ++h)
+#pragma unroll
+          for (uint32_t e = 0; e < 4; ++e) {
+            w[h][e] = 0, jn[h][e] = 0;
+            const uint32_t y = x[h][e];
+            if (!(y & kJRes) && y >= lo) {
+              jn[h][e] = J[y];
+              w[h][e] = kAll ? ~0ull : lm[y >> 6];
+            }
+          }
+#pragma unroll
+        for (uint32_t h = 0; h < kRows; ++h)
+#pragma unroll
+          for (uint32_t e = 0; e < 4; ++e) {
+            const uint32_t y = x[h][e];
+            if (!(y & kJRes) && y >= lo) x[h][e] = (w[h][e] >> (y & 63)) & 1 ? jn[h][e] : kJRes | *po.at(y);
+          }
+      }
+      uint32_t out[kRows];
+#pragma unroll
+      for (uint32_t h = 0; h < kRows; ++h) {
+        const u32x4 y = x[h];
+        if (!((y.x | y.w) & kJRes) && y.y == y.x + 1 && y.z == y.x + 2 && y.w == y.x + 3 &&
+            (y.x >> a.s_log2) == (y.w >> a.s_log2)) {  // four consecutive settled bytes
+          out[h] = *reinterpret_cast<const AX_GLOBAL u32_u*>(po.at(y.x));
+        } else {
+          out[h] = 0;
+#pragma unroll
+          for (uint32_t e = 0; e < 4; ++e)
+            out[h] |= (y[e] & kJRes ? y[e] & 0xFFu : uint32_t(*po.at(y[e]))) << (8 * e);
+        }
+      }
+#pragma unroll
+      for (uint32_t h = 0; h < kRows; ++h) {
+        if (!bits[h]) continue;
+        const gbytes o = po.at(p[h]);
+        if (bits[h] == 0xFu) {
+          *reinterpret_cast<AX_GLOBAL uint32_t*>(o) = out[h];
+        } else {
+#pragma unroll
+          for (uint32_t e = 0; e < 4; ++e)
+            if ((bits[h] >> e) & 1) o[e] = uint8_t(out[h] >> (8 * e));
+        }
+      }
+    }
+  }
+}
+
 // A range decode's slot table: the window's blocks (one window) take slots
 // 0, 1, ... in window order.
 __global__ void k_slots(uint32_t* slot, const WinBlock* wbl, uint32_t n_items) {
@@ -2206,9 +2943,9 @@ struct PrepArgs {
   uint32_t n_counts;
   uint32_t* pbits;
   uint32_t n_pbits;
-  uint64_t* lmap;  // null: no jump in this window
+  uint64_t* lmap;
   uint64_t n_lmap;
-  uint8_t** ibase;
+  uint8_t** ibase;  // null: no pointer jumping in this window
   const JobDev* jobs;
   const WinBlock* wbl;
   uint32_t n_items;
@@ -2220,8 +2957,8 @@ __global__ __launch_bounds__(kCopyThreads) void k_window_prep(PrepArgs a) {
   const uint64_t i0 = uint64_t(blockIdx.x) * kCopyThreads + threadIdx.x, step = uint64_t(gridDim.x) * kCopyThreads;
   for (uint64_t i = i0; i < a.n_counts; i += step) a.counts[i] = 0;
   for (uint64_t i = i0; i < a.n_pbits; i += step) a.pbits[i] = 0;
-  if (!a.lmap) return;
   for (uint64_t i = i0; i < a.n_lmap; i += step) a.lmap[i] = 0;
+  if (!a.ibase) return;
   for (uint64_t x = i0; x < a.n_items; x += step) {
     const WinBlock wb = a.wbl[x];
     const JobDev& jd = a.jobs[wb.job];
@@ -2239,8 +2976,8 @@ namespace ax {
 
 struct Layout {
   uint64_t status, nsym, lit, cmd, off, len, tok, tblk, cov, done, counts, jflags, list0, list1, llist, pbits, pcnt,
-      plist, lmap, mcov, amap, ibase, wlist, total;
-  uint64_t jbytes;  // the jump array: the stream slots, dead once the parse is through
+      plist, lmap, amap, ibase, wlist, total;
+  uint64_t jbytes;  // the jump array: the stream slots but the commands', dead once the parse is through
   uint64_t sub_cap;
 };
 
@@ -2255,6 +2992,7 @@ struct Plan {
     uint64_t at;       // first WinBlock
     uint32_t items;    // blocks
     uint32_t tok;      // tokens
+    uint32_t deep;     // its first blocks: those of deep archives
   };
   std::vector<Win> wins;
   uint32_t max_items = 0, max_tok = 0, slot_b = 0, off_cap = 0, len_cap = 0;
@@ -2329,8 +3067,8 @@ static Layout make_layout(const Plan& P) {
   uint64_t at = 0;
   L.status = at, at = align256(at + sizeof(DevStatus));
   L.nsym = at, at = align256(at + 16 * W);
-  L.lit = at, at = align256(at + W * P.slot_b);
   L.cmd = at, at = align256(at + W * P.slot_b);
+  L.lit = at, at = align256(at + W * P.slot_b);
   L.off = at, at = align256(at + W * P.off_cap);
   L.len = at, at = align256(at + W * P.len_cap);
   L.tok = at, at = align256(at + 16 * T);
@@ -2354,13 +3092,13 @@ static Layout make_layout(const Plan& P) {
   L.pcnt = at, at = align256(at + 4 * ((T + 31) / 32 / kPackWords + 1));
   L.plist = at, at = align256(at + 4 * T);
   L.lmap = at, at = align256(at + W * P.slot_b / 8);
-  L.mcov = at, at = align256(at + W * P.slot_b / 8);
   L.ibase = at, at = align256(at + 8 * W);
   L.wlist = at, at = align256(at + W * P.slot_b / 16);                        // one u32 per map word
   L.amap = at, at = align256(at + W * P.slot_b / 8);
   L.total = at;
-  // the jump array (4 B per window position) reuses the four stream slots,
-  // dead once the parse is through: at least 5 B per window position
+  // the jump array (4 B per window position) reuses the literal, offset and
+  // length slots, dead once the parse is through: at least 4 B per window
+  // position (the command slots hold the records by then)
   L.jbytes = L.len + W * P.len_cap - L.lit;
   return L;
 }
@@ -2379,6 +3117,20 @@ static uint32_t jump_pass_bound(uint64_t tok) {
   while (p < kJPasses && span <= tok) ++p, span *= 3;
   return p;
 }
+
+// Archives taken to be deep: those compressed at least kDeepRatio times.  Such
+// ratios need matches over most of the bytes, hence chains (text: 5.2, all
+// bytes marked 764 us for 80 MiB against 1470 us with walks first); marking
+// costs four bytes of jump array per position, so where few bytes are copied
+// walks win (254 MB DNA, ratio 2.55: 787 against 1660 us; 32 MiB reads, 1.76:
+// 262 against 281 us).  In small plans the marking is cheap and its shorter
+// chain of loads counts: 64 KiB / 4 MiB DNA 94 / 122 us against 140 / 148 us;
+// at 16 MiB the walks win again (172 against 191 us).
+constexpr uint64_t kDeepRatio = 3;
+constexpr uint64_t kDeepSmall = 8u << 20;  // positions of a small plan
+// So many deep blocks are finished run by run (eight launches, each reading
+// settled bytes); fewer in one launch that follows the entries.
+constexpr uint32_t kPartBlocks = 2048;
 
 // Host tables of a plan: jobs, window blocks, windows, maxima.
 static int build_tables(Plan* P, const std::vector<JobSpec>& specs) {
@@ -2413,7 +3165,7 @@ static int build_tables(Plan* P, const std::vector<JobSpec>& specs) {
     P->gtok.reserve(gblocks);
     // windows: consecutive (job, block) items, at most kWindowBlocks blocks
     // and kWindowTokens tokens each
-    Plan::Win cur{0, 0, 0};
+    Plan::Win cur{0, 0, 0, 0};
     auto close = [&]() {
       if (!cur.items) return;
       for (uint64_t i = cur.at; i < cur.at + cur.items;) {  // per-job extents inside the window
@@ -2429,18 +3181,25 @@ static int build_tables(Plan* P, const std::vector<JobSpec>& specs) {
       P->max_tok = std::max(P->max_tok, cur.tok);
       P->n_tokens += cur.tok;
       P->wins.push_back(cur);
-      cur = Plan::Win{P->wbl.size(), 0, 0};
+      cur = Plan::Win{P->wbl.size(), 0, 0, 0};
     };
-    // jobs enter the windows densest first (matches per block): a window runs
-    // as long as its deepest dependency chain, and match-dense archives carry
-    // the deep chains, so they share windows instead of lengthening every one
+    // jobs enter the windows deep archives first, then densest first (matches
+    // per block): a window runs as long as its deepest dependency chain, and
+    // match-dense archives carry the deep chains, so they share windows
+    // instead of lengthening every one
+    const bool small = gblocks * P->slot_b <= kDeepSmall;
+    auto deep = [&](size_t j) {
+      return small || specs[j].dec->info.payload_bytes < specs[j].dec->info.n_bytes / kDeepRatio;
+    };
     std::vector<size_t> order(specs.size());
     for (size_t j = 0; j < order.size(); ++j) order[j] = j;
     auto density = [&](size_t j) {
       const aceapex_decoder* d = specs[j].dec;
       return d->info.n_blocks ? double(d->mpre[d->info.n_blocks]) / double(d->info.n_blocks) : 0.0;
     };
-    std::stable_sort(order.begin(), order.end(), [&](size_t x, size_t y) { return density(x) > density(y); });
+    std::stable_sort(order.begin(), order.end(), [&](size_t x, size_t y) {
+      return deep(x) != deep(y) ? deep(x) : density(x) > density(y);
+    });
     for (const size_t j : order) {
       const aceapex_decoder* d = specs[j].dec;
       const uint64_t nb = specs[j].blocks.empty() ? d->info.n_blocks : specs[j].blocks.size();
@@ -2452,6 +3211,7 @@ static int build_tables(Plan* P, const std::vector<JobSpec>& specs) {
         P->wbl.push_back(WinBlock{b, uint32_t(j), cur.tok, 0, 0});
         P->gtok.push_back(d->mpre[b]);
         cur.items++;
+        cur.deep += deep(j);
         cur.tok += uint32_t(nt);
       }
     }
@@ -2578,6 +3338,8 @@ int plan_reset(Plan* P, const std::vector<JobSpec>& specs, hipStream_t s) {
   return AX_OK;
 }
 
+static bool roots_schedule(const Plan* P, int copy_mode);
+
 uint64_t plan_workspace_for(const aceapex_decoder* d, uint64_t max_blocks, uint64_t max_tokens) {
   Plan P;
   P.max_items = uint32_t(max_blocks);
@@ -2598,6 +3360,7 @@ int plan_set_slots(Plan* P, uint32_t* slot, hipStream_t s) {
   hipError_t e = hipGetLastError();
   return e == hipSuccess ? AX_OK : hip_fail(e, "slot table");
 }
+bool plan_roots(const Plan* P) { return roots_schedule(P, AX_COPY_PERIODIC); }
 void plan_set_learn(Plan* P, bool learn) { P->learn = learn; }
 
 int plan_parse_tokens(Plan* P, void* d_work, uint64_t work_len, hipStream_t s, uint64_t* src, uint64_t* dstlen) {
@@ -2622,7 +3385,7 @@ int plan_parse_tokens(Plan* P, void* d_work, uint64_t work_len, hipStream_t s, u
     hipLaunchKernelGGL(k_ans, dim3(4 * W.items), dim3(64), 0, s, aa);
     ParseArgs pa{P->d_jobs, wbl, W.items, W.tok, P->slot_b, w + L.lit, w + L.cmd, w + L.off, w + L.len, P->off_cap,
                  P->len_cap, reinterpret_cast<const uint32_t*>(w + L.nsym), reinterpret_cast<uint64_t*>(w + L.tok),
-                 reinterpret_cast<uint32_t*>(w + L.tblk), w + L.done, st, 0, nullptr};
+                 nullptr, nullptr, st, 0};
     hipLaunchKernelGGL((k_parse<OutDirect, false>), dim3(W.items), dim3(kParseThreads), 0, s, pa);
     try {
       tk.resize(2ull * W.tok);
@@ -2814,6 +3577,55 @@ int plan_stage_ms(Plan* P, float* ans, float* parse, float* copy, float* remaind
   return AX_OK;
 }
 
+// Whether a decode runs the roots schedule (k_roots): the default one; any
+// knob of the rounds schedule off its default, or the serial copy mode, asks
+// for the rounds.
+static bool roots_schedule(const Plan* P, int copy_mode) {
+  const PlanOptions d;
+  const PlanOptions& o = P->opt;
+  return copy_mode == AX_COPY_PERIODIC && o.bulk_rounds == d.bulk_rounds && o.fill_round == d.fill_round &&
+         o.fill_tail == d.fill_tail && o.tail_chunks == d.tail_chunks && o.round0_tile == d.round0_tile &&
+         o.tail_mode == d.tail_mode && o.jump_passes == d.jump_passes;
+}
+
+// The roots match layer of one window.
+template <class O>
+static void enqueue_roots(Plan* P, const Plan::Win& W, const WinBlock* wbl, uint8_t* w, hipStream_t s, hipEvent_t* ev) {
+  const Layout& L = P->lay;
+  DevStatus* st = reinterpret_cast<DevStatus*>(w + L.status);
+  const uint32_t s_log2 = uint32_t(__builtin_ctz(P->slot_b));
+  uint32_t* J = reinterpret_cast<uint32_t*>(w + L.lit);  // the stream slots, dead once the parse is through
+  uint64_t* lmap = reinterpret_cast<uint64_t*>(w + L.lmap);
+  const RootArgs ra{P->d_jobs, wbl, W.items, W.tok, s_log2, reinterpret_cast<const uint64_t*>(w + L.tok), w + L.cmd,
+                    J, lmap, st, W.deep,
+                    uint64_t(W.deep) << s_log2 <= kDeepSmall ? kMarkSmallLog2 : kMarkLog2};
+  const uint32_t shallow = W.items - W.deep;
+  if (W.deep) hipLaunchKernelGGL(k_mark<O>, dim3(W.deep << (s_log2 - ra.mark_log2)), dim3(kCopyThreads), 0, s, ra);
+  if (shallow) hipLaunchKernelGGL(k_roots<O>, dim3(shallow), dim3(kCopyThreads), 0, s, ra);
+  if (ev) (void)hipEventRecord(ev[3], s);
+  SweepArgs sa{s_log2, J, lmap, P->d_jobs, wbl, P->jobs.size() == 1 ? 1u : 0u,
+               reinterpret_cast<uint8_t* const*>(w + L.ibase), st, 0, 0, 0};
+  auto resolve = [&](uint32_t b0, uint32_t b1, bool all) {
+    if (b0 == b1) return;
+    // a wave per chunk of map words
+    const uint64_t waves = (uint64_t(b1 - b0) << (s_log2 - 6)) / kSweepChunk;
+    const uint32_t grid = std::max(1u, uint32_t(std::min<uint64_t>((waves + 3) / 4, kSweepGrid)));
+    const dim3 sgrid((grid + kXcds - 1) / kXcds * kXcds);
+    sa.b0 = b0, sa.b1 = b1, sa.settled = 0;
+    if (all) hipLaunchKernelGGL(k_sweep<true>, sgrid, dim3(kCopyThreads), 0, s, sa);
+    else hipLaunchKernelGGL(k_sweep<false>, sgrid, dim3(kCopyThreads), 0, s, sa);
+    const uint32_t parts = all && b1 - b0 >= kPartBlocks ? kXcds : 1;
+    for (uint32_t k = 0; k < parts; ++k) {
+      sa.b0 = b0 + uint32_t(uint64_t(b1 - b0) * k / parts), sa.b1 = b0 + uint32_t(uint64_t(b1 - b0) * (k + 1) / parts);
+      sa.settled = parts > 1;
+      if (all) hipLaunchKernelGGL(k_finish<true>, dim3(grid), dim3(kCopyThreads), 0, s, sa);
+      else hipLaunchKernelGGL(k_finish<false>, dim3(grid), dim3(kCopyThreads), 0, s, sa);
+    }
+  };
+  resolve(0, W.deep, true);
+  resolve(W.deep, W.items, false);
+}
+
 // Enqueue the plan's kernels on s (also used inside a graph capture).
 template <class O>
 static void enqueue_out(Plan* P, uint8_t* w, int copy_mode, hipStream_t s, bool timed, bool feedback) {
@@ -2826,6 +3638,7 @@ static void enqueue_out(Plan* P, uint8_t* w, int copy_mode, hipStream_t s, bool 
     const WinBlock* wbl = P->d_wbl + W.at;
     uint32_t* counts = reinterpret_cast<uint32_t*>(w + L.counts);
     const uint32_t ntok = W.tok;
+    const bool roots = roots_schedule(P, copy_mode);
     const bool jump = P->opt.tail_mode == 0 && copy_mode != AX_COPY_SERIAL;
     const uint32_t n_words = (ntok + 31) / 32;
     const uint64_t mwords = uint64_t(W.items) * (P->slot_b / 64);  // leftover-map words
@@ -2833,11 +3646,13 @@ static void enqueue_out(Plan* P, uint8_t* w, int copy_mode, hipStream_t s, bool 
     const uint32_t jgrid = uint32_t(std::min<uint64_t>((mwords + 31) / 32, kJMaxGrid));
     {
       const bool jmap = jump && ntok;
-      const PrepArgs pr{st, int(first), counts, uint32_t((L.jflags - L.counts) / 4 + kJPasses * kJShards * kJFlagStride),
-                        reinterpret_cast<uint32_t*>(w + L.pbits), ntok ? n_words : 0u,
-                        jmap ? reinterpret_cast<uint64_t*>(w + L.lmap) : nullptr, mwords,
-                        reinterpret_cast<uint8_t**>(w + L.ibase), P->d_jobs, wbl, W.items};
-      hipLaunchKernelGGL(k_window_prep<O>, dim3(std::max(1u, jgrid)), dim3(kCopyThreads), 0, s, pr);
+      const uint32_t n_counts = uint32_t((L.jflags - L.counts) / 4 + kJPasses * kJShards * kJFlagStride);
+      const PrepArgs pr{st, int(first), counts, roots ? 0u : n_counts, reinterpret_cast<uint32_t*>(w + L.pbits),
+                        ntok && !roots ? n_words : 0u, reinterpret_cast<uint64_t*>(w + L.lmap), jmap && !roots ? mwords : 0u,
+                        jmap && !(roots && P->jobs.size() == 1) ? reinterpret_cast<uint8_t**>(w + L.ibase) : nullptr, P->d_jobs,
+                        wbl, W.items};
+      const uint32_t pgrid = roots ? (W.items + kCopyThreads - 1) / kCopyThreads : jgrid;
+      hipLaunchKernelGGL(k_window_prep<O>, dim3(std::max(1u, pgrid)), dim3(kCopyThreads), 0, s, pr);
     }
     AnsArgs aa{P->d_jobs, wbl, W.items, P->slot_b, w + L.lit, w + L.cmd, w + L.off, w + L.len, P->off_cap,
                P->len_cap, reinterpret_cast<uint32_t*>(w + L.nsym), st};
@@ -2846,13 +3661,19 @@ static void enqueue_out(Plan* P, uint8_t* w, int copy_mode, hipStream_t s, bool 
     hipLaunchKernelGGL(k_ans, dim3(4 * W.items), dim3(64), 0, s, aa);
     if (ev) (void)hipEventRecord(ev[1], s);
     const int bulk = P->wbulk[wi] ? int(P->wbulk[wi]) : P->opt.bulk_rounds;
+    const bool recs = roots || bulk <= 1;
     ParseArgs pa{P->d_jobs, wbl, W.items, W.tok, P->slot_b, w + L.lit, w + L.cmd, w + L.off, w + L.len, P->off_cap,
                  P->len_cap, reinterpret_cast<const uint32_t*>(w + L.nsym), reinterpret_cast<uint64_t*>(w + L.tok),
-                 reinterpret_cast<uint32_t*>(w + L.tblk), w + L.done, st, 1,
-                 bulk <= 1 ? reinterpret_cast<uint16_t*>(w + L.mcov) : nullptr};
-    if (pa.mcov) hipLaunchKernelGGL((k_parse<O, true>), dim3(W.items), dim3(kParseThreads), 0, s, pa);
+                 roots ? nullptr : reinterpret_cast<uint32_t*>(w + L.tblk), w + L.done, st, 1};
+    if (recs) hipLaunchKernelGGL((k_parse<O, true>), dim3(W.items), dim3(kParseThreads), 0, s, pa);
     else hipLaunchKernelGGL((k_parse<O, false>), dim3(W.items), dim3(kParseThreads), 0, s, pa);
     if (ev) (void)hipEventRecord(ev[2], s);
+    if (roots) {
+      if (ntok) enqueue_roots<O>(P, W, wbl, w, s, ev);
+      else if (ev) (void)hipEventRecord(ev[3], s);
+      if (ev) (void)hipEventRecord(ev[4], s);
+      continue;
+    }
     const int last_mark = jump ? kMarkJump : kMarkList;
     if (ntok) {
       uint32_t* lists[2] = {reinterpret_cast<uint32_t*>(w + L.list0), reinterpret_cast<uint32_t*>(w + L.list1)};
@@ -2865,7 +3686,7 @@ static void enqueue_out(Plan* P, uint8_t* w, int copy_mode, hipStream_t s, bool 
                   reinterpret_cast<uint32_t*>(w + L.pbits), reinterpret_cast<const uint32_t*>(w + L.plist),
                   bulk <= 1 ? last_mark : 0, 1ull << 22, copy_mode == AX_COPY_SERIAL, P->opt.fill_round,
                   P->opt.fill_tail, uint32_t(P->opt.tail_chunks), reinterpret_cast<uint32_t*>(w + L.lit),
-                  reinterpret_cast<uint64_t*>(w + L.lmap), P->slot_b, pa.mcov ? reinterpret_cast<const uint64_t*>(w + L.mcov) : nullptr,
+                  reinterpret_cast<uint64_t*>(w + L.lmap), P->slot_b, recs ? w + L.cmd : nullptr,
                   P->jobs.size() == 1 ? 1u : 0u};
       // pointer jumping over window positions (the deep remainder); the
       // jump array is the stream slots, dead once the parse is through
@@ -2875,7 +3696,7 @@ static void enqueue_out(Plan* P, uint8_t* w, int copy_mode, hipStream_t s, bool 
                   reinterpret_cast<uint8_t**>(w + L.ibase), uint32_t(__builtin_ctz(P->slot_b)),
                   nullptr, nullptr, uint32_t(L.sub_cap), reinterpret_cast<uint32_t*>(w + L.wlist), st, 0};
       const uint32_t grid = uint32_t(std::min<uint64_t>((ntok + kCopyThreads - 1) / kCopyThreads, kMaxRoundGrid));
-      if (P->opt.round0_tile && ca.mcov)
+      if (P->opt.round0_tile && ca.cmd)
         hipLaunchKernelGGL((k_round0<O, true>), dim3(W.items), dim3(kCopyThreads), 0, s, ca);
       else if (P->opt.round0_tile)
         hipLaunchKernelGGL((k_round0<O, false>), dim3(W.items), dim3(kCopyThreads), 0, s, ca);
@@ -2989,8 +3810,9 @@ static int run_plan(Plan* P, void* d_work, uint64_t work_len, int copy_mode, hip
     P->graph_stale = P->graph != nullptr;  // counts changed
   }
   if (P->graph_stale && !no_alloc) (void)hipGraphExecDestroy(P->graph), P->graph = nullptr, P->graph_stale = false;
-  const bool fb_jump = !P->jsettled && P->opt.tail_mode == 0 && !P->opt.jump_passes && copy_mode != AX_COPY_SERIAL;
-  const bool fb_bulk = P->bulk_auto && !P->bsettled;
+  const bool rounds = !roots_schedule(P, copy_mode);
+  const bool fb_jump = rounds && !P->jsettled && P->opt.tail_mode == 0 && !P->opt.jump_passes && copy_mode != AX_COPY_SERIAL;
+  const bool fb_bulk = rounds && P->bulk_auto && !P->bsettled;
   const bool feedback = P->learn && (fb_jump || fb_bulk) && !P->jfeed_pending && !P->wins.empty() &&
                         P->jused_cap >= P->wins.size() && P->jfed;
   if (feedback) std::fill(P->h_jused, P->h_jused + 2 * P->wins.size(), 0u);

@@ -53,6 +53,8 @@ int plan_reset(Plan* p, const std::vector<JobSpec>& jobs, hipStream_t s);
 // Workspace of a one-window plan of decoder d with these maxima.
 uint64_t plan_workspace_for(const aceapex_decoder* d, uint64_t max_blocks, uint64_t max_tokens);
 void plan_copy_options(Plan* dst, const Plan* src);
+// Whether the plan's options leave its match layer to the default schedule.
+bool plan_roots(const Plan* p);
 // Enqueue the slot-table entries of a mapped plan's blocks on s.
 int plan_set_slots(Plan* p, uint32_t* slot, hipStream_t s);
 // Whether a plan learns its jump-pass counts from its own decodes (on by
