@@ -66,7 +66,7 @@ typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
 
 constexpr uint32_t kMaxB = 16384;           // largest block the device path decodes
 constexpr uint32_t kParseThreads = 256;
-constexpr uint32_t kOffStage = 1792;        // offset-stream bytes staged in LDS by k_parse
+constexpr uint32_t kOffStage = 3072;        // offset-stream bytes staged in LDS by k_parse
 constexpr uint32_t kLenStage = 256;         // length-stream bytes staged in LDS by k_parse
 constexpr uint32_t kLenBpt = 1, kOffBpt = 2;  // LEB bytes per thread per pass: length / offset streams
 constexpr uint32_t kCopyThreads = 256;      // match-layer workgroup
@@ -479,15 +479,17 @@ struct ParseShared {
   uint16_t rundelta[kParseThreads];  // per run: output position - literal index
   uint16_t runbeg[kParseThreads];    // per run: first output position
   uint16_t runend[kParseThreads];    // per run: one past its last output position
-  uint8_t offb[kOffStage];        // the block's decoded offset stream, when it fits
-  uint8_t lenb[kLenStage];        // the block's decoded length stream, when it fits
+  u32x4 below[17];                // below[k]: sixteen bytes, the first k of them 0xFF
+  // the block's decoded offset and length streams, when they fit, and where
+  // each of their values ends (one past its last byte)
+  __attribute__((aligned(16))) uint8_t offb[kOffStage + 16];
+  __attribute__((aligned(16))) uint8_t lenb[kLenStage + 16];
+  uint16_t offend[kOffStage];
+  uint16_t lenend[kLenStage];
   uint64_t offval[kParseThreads];
   uint64_t wsum[4][2];
   HMap wmap[4];
-  union {
-    uint64_t cdist[kParseThreads];   // distance of the explicit match at each chunk position
-    uint32_t lenval[kParseThreads];  // length extensions: read before cdist is written (a barrier apart)
-  };
+  uint64_t cdist[kParseThreads];  // distance of the explicit match at each chunk position
   uint64_t last4[4];              // the chunk's last explicit-match distances, newest first
   uint32_t wterm[4];
   int32_t wlast[4];
@@ -532,7 +534,8 @@ __device__ inline uint32_t wave_incl_sum32(uint32_t x) {
 }
 
 // Block-wide exclusive scan of a u64 holding two u32 sums (the halves are
-// scanned separately: no half may carry), 256 threads.
+// scanned separately: no half may carry), 256 threads.  One barrier: a slot is
+// written again only after a later one.
 __device__ inline uint64_t block_excl_sum64(uint64_t v, uint64_t* total, ParseShared& sh, int slotk) {
   const uint32_t lane = lane_id(), wv = threadIdx.x >> 6;
   const uint64_t x = wave_incl_sum32(uint32_t(v)) | (uint64_t(wave_incl_sum32(uint32_t(v >> 32))) << 32);
@@ -544,7 +547,6 @@ __device__ inline uint64_t block_excl_sum64(uint64_t v, uint64_t* total, ParseSh
     if (k < wv) pre += t;
     tot += t;
   }
-  __syncthreads();
   *total = tot;
   return pre + x - v;
 }
@@ -571,7 +573,6 @@ __device__ inline HMap block_excl_map(HMap m, HMap* total, ParseShared& sh) {
     if (k < wv) pre = map_after(sh.wmap[k], pre);
     tot = map_after(sh.wmap[k], tot);
   }
-  __syncthreads();
   *total = tot;
   return map_after(map_dpp<kDppWaveShr1, 0xF>(x), pre);  // inclusive of the previous lane
 }
@@ -661,9 +662,46 @@ __device__ bool leb_values(Src src, uint32_t n, uint32_t* cursor, uint32_t count
   return true;
 }
 
-// Six waves per SIMD (at most 80 VGPRs).
+// The terminators (bytes below 0x80) among the first n bytes of v, one bit per byte.
+__device__ inline uint32_t leb_ends(uint4 v, uint32_t n) {
+  auto four = [](uint32_t w) {
+    w = (~w >> 7) & 0x01010101u;
+    return (w | (w >> 7) | (w >> 14) | (w >> 21)) & 0xFu;
+  };
+  const uint32_t m = four(v.x) | (four(v.y) << 4) | (four(v.z) << 8) | (four(v.w) << 12);
+  return n >= 16 ? m : m & ((1u << n) - 1u);
+}
+
+// Value k of a staged stream: its bytes are src[end[k - 1], end[k]).  False on
+// a value longer than ten bytes or beyond 64 bits.  (The bytes behind a value
+// may be read and are masked off: the stages are padded.)
+__device__ inline bool leb_staged(const uint8_t* src, const uint16_t* end, uint32_t k, uint64_t& v) {
+  const uint32_t b = k ? end[k - 1] : 0u, n = end[k] - b;
+  const uint32_t* const w = reinterpret_cast<const uint32_t*>(src) + (b >> 2);
+  const uint32_t w0 = w[0], w1 = w[1], w2 = w[2], w3 = w[3];
+  uint64_t x = __builtin_amdgcn_alignbyte(w1, w0, b) | (uint64_t(__builtin_amdgcn_alignbyte(w2, w1, b)) << 32);
+  const uint32_t hi = n > 8 ? __builtin_amdgcn_alignbyte(w3, w2, b) : 0u;  // bytes 8 and 9
+  if (n < 8) x &= (1ull << (8 * n)) - 1;
+  // seven bits of each of eight bytes, in pairs, fours, then all
+  x = (x & 0x007F007F007F007Full) | ((x & 0x7F007F007F007F00ull) >> 1);
+  x = (x & 0x00003FFF00003FFFull) | ((x & 0x3FFF00003FFF0000ull) >> 2);
+  v = (x & 0x0FFFFFFFull) | ((x >> 32) << 28) | (uint64_t(hi & 0x7Fu) << 56);
+  if (n <= 9) return true;
+  v |= uint64_t((hi >> 8) & 1u) << 63;
+  return n == 10 && (hi & 0xFF00u) <= 0x100u;
+}
+
+// Seven waves per SIMD (at most 72 VGPRs), as many as the LDS allows (six: 254 MB
+// DNA 741 instead of 728 us, eight: 768).
+//
+// A chunk of 256 commands is a chain of block-wide steps: with few blocks in
+// flight its latency counts, with many the instructions issued.  The values
+// of the offset and length streams are therefore found once per block (one
+// scan over the staged bytes lists where every value ends) and read by the
+// command that needs them, instead of a scan over a window of the stream for
+// every chunk: 64 KiB of DNA parse in 42 -> 29 us, 254 MB in 253 -> 208 us.
 template <class O, bool kRecs>
-__global__ __launch_bounds__(kParseThreads, 6) void k_parse(ParseArgs a) {
+__global__ __launch_bounds__(kParseThreads, 7) void k_parse(ParseArgs a) {
   __shared__ ParseShared sh;
   const uint32_t item = blockIdx.x, t = threadIdx.x;
   const WinBlock wb = a.wbl[item];
@@ -700,17 +738,34 @@ __global__ __launch_bounds__(kParseThreads, 6) void k_parse(ParseArgs a) {
   uint4 po = {0, 0, 0, 0}, pl = {0, 0, 0, 0};
   if (16 * t < min(kOffStage, a.off_cap)) po = *reinterpret_cast<const uint4*>(offs + 16 * t);
   if (16 * t < min(kLenStage, a.len_cap)) pl = *reinterpret_cast<const uint4*>(lens + 16 * t);
-  if (n_off <= kOffStage && 16 * t < n_off) *reinterpret_cast<uint4*>(sh.offb + 16 * t) = po;
-  if (n_len <= kLenStage && 16 * t < n_len) *reinterpret_cast<uint4*>(sh.lenb + 16 * t) = pl;
-  __syncthreads();
-  bool failed = sh.bad != 0;
-  // the streams are read from LDS when staged, else from global memory (two
-  // instantiations, so neither path goes through flat addressing)
   const bool off_lds = n_off <= kOffStage, len_lds = n_len <= kLenStage;
+  uint32_t oe = 0, le = 0;
+  if (off_lds && 16 * t < n_off) {
+    *reinterpret_cast<uint4*>(sh.offb + 16 * t) = po;
+    oe = leb_ends(po, n_off - 16 * t);
+  }
+  if (len_lds && 16 * t < n_len) {
+    *reinterpret_cast<uint4*>(sh.lenb + 16 * t) = pl;
+    le = leb_ends(pl, n_len - 16 * t);
+  }
+  if (t < 17) {
+    const uint64_t lo = t < 8 ? (1ull << (8 * t)) - 1 : ~0ull;
+    const uint64_t hi = t <= 8 ? 0 : t < 16 ? (1ull << (8 * (t - 8))) - 1 : ~0ull;
+    sh.below[t] = u32x4{uint32_t(lo), uint32_t(lo >> 32), uint32_t(hi), uint32_t(hi >> 32)};
+  }
+  if (t < kMaxB / 64) sh.runbits[t] = 0;
+  // where the streams' values end; off_n and len_n count them
+  uint64_t ends;
+  const uint64_t eex = block_excl_sum64(uint64_t(__popc(oe)) | (uint64_t(__popc(le)) << 32), &ends, sh, 1);
+  const uint32_t off_n = uint32_t(ends), len_n = uint32_t(ends >> 32);
+  for (uint32_t k = uint32_t(eex); oe; oe &= oe - 1, ++k) sh.offend[k] = uint16_t(16 * t + __builtin_ctz(oe) + 1);
+  for (uint32_t k = uint32_t(eex >> 32); le; le &= le - 1, ++k) sh.lenend[k] = uint16_t(16 * t + __builtin_ctz(le) + 1);
+  bool failed = sh.bad != 0;
+  // streams too long for their stage are read from global memory, a chunk's values at a time
   const AX_GLOBAL uint8_t* const offg = gp(offs);
   const AX_GLOBAL uint8_t* const leng = gp(lens);
 
-  uint32_t dst = 0, litp = 0, offc = 0, lenc = 0;
+  uint32_t dst = 0, litp = 0, offc = 0, lenc = 0;  // offc, lenc: staged, values taken; else bytes
   uint64_t ntok = 0;
   uint64_t hist[4] = {1, 2, 3, 4};
   for (uint32_t c0 = 0; c0 < n_cmd && !failed; c0 += kParseThreads) {
@@ -731,30 +786,39 @@ __global__ __launch_bounds__(kParseThreads, 6) void k_parse(ParseArgs a) {
     const uint32_t n_esc = uint32_t(ctot & 0xFFFF), n_k1 = uint32_t((ctot >> 16) & 0xFFFF);
     const uint32_t n_tokc = uint32_t(ctot >> 48);
     // length and offset values of this chunk
-    uint64_t* lv64 = sh.offval;  // reuse: lengths first, then offsets
-    if (n_esc) {  // most chunks hold no escaped length (n_esc is the same for the whole block)
-      if (!(len_lds ? leb_values<kLenBpt>(static_cast<const uint8_t*>(sh.lenb), n_len, &lenc, n_esc, lv64, sh)
-                    : leb_values<kLenBpt>(leng, n_len, &lenc, n_esc, lv64, sh))) {
+    uint32_t ext = 0;
+    if (len_lds) {
+      if (esc) {
+        uint64_t e = 0;
+        if (lenc + esc_i < len_n && leb_staged(sh.lenb, sh.lenend, lenc + esc_i, e) && e <= B) ext = uint32_t(e);
+        else bad = true;
+      }
+      lenc += n_esc;
+    } else if (n_esc) {  // n_esc is the same for the whole block
+      if (!leb_values<kLenBpt>(leng, n_len, &lenc, n_esc, sh.offval, sh)) {
         failed = true;
         break;
       }
-      if (t < n_esc) {
-        const uint64_t e = lv64[t];
-        sh.lenval[t] = e > B ? 0xFFFFFFFFu : uint32_t(e);
+      if (esc) {
+        const uint64_t e = sh.offval[esc_i];
+        ext = uint32_t(e);
+        bad |= e > B;
       }
       __syncthreads();
     }
-    if (!(off_lds ? leb_values<kOffBpt>(static_cast<const uint8_t*>(sh.offb), n_off, &offc, n_k1, sh.offval, sh)
-                  : leb_values<kOffBpt>(offg, n_off, &offc, n_k1, sh.offval, sh))) {
-      failed = true;
-      break;
+    uint64_t off = 0;  // an explicit match's source
+    if (off_lds) {
+      if (is1) bad |= offc + k1_i >= off_n || !leb_staged(sh.offb, sh.offend, offc + k1_i, off);
+      offc += n_k1;
+    } else {
+      if (!leb_values<kOffBpt>(offg, n_off, &offc, n_k1, sh.offval, sh)) {
+        failed = true;
+        break;
+      }
+      if (is1) off = sh.offval[k1_i];
     }
     uint32_t len = 0;
-    if (valid) {
-      const uint32_t ext = esc ? sh.lenval[esc_i] : 0u;
-      bad |= ext == 0xFFFFFFFFu;
-      len = bad ? 0 : v + (kind == 0 ? 1u : mm) + ext;
-    }
+    if (valid && !bad) len = v + (kind == 0 ? 1u : mm) + ext;
     const uint64_t lp = uint64_t(len) | (uint64_t(is0 ? len : 0u) << 32);
     uint64_t ptot;
     const uint64_t pex = block_excl_sum64(lp, &ptot, sh, 1);
@@ -765,7 +829,7 @@ __global__ __launch_bounds__(kParseThreads, 6) void k_parse(ParseArgs a) {
     const uint64_t absdst = bs + cdst;
     uint64_t src = 0;
     if (is1) {
-      src = sh.offval[k1_i];
+      src = off;
       if (src >= absdst) bad = true;
       else sh.cdist[t] = absdst - src;
     }
@@ -810,8 +874,6 @@ __global__ __launch_bounds__(kParseThreads, 6) void k_parse(ParseArgs a) {
       }
     }
     // literal runs: starts in the block's output positions
-    for (uint32_t w = t; w < B / 64; w += kParseThreads) sh.runbits[w] = 0;
-    __syncthreads();
     if (is0 && !bad && len) {
       atomicOr(reinterpret_cast<uint32_t*>(sh.runbits) + (cdst >> 5), 1u << (cdst & 31));
       sh.rundelta[run_i] = uint16_t(cdst - clit);
@@ -847,14 +909,7 @@ __global__ __launch_bounds__(kParseThreads, 6) void k_parse(ParseArgs a) {
         // still inside the workspace)
         const u32x4 e = *reinterpret_cast<const AX_GLOBAL u32x4_u*>(litg + l0);
         const uint32_t m16 = ((1u << (x1 - 16 * c)) - 1u) & ~((1u << (x0 - 16 * c)) - 1u);
-        // byte i of the group's mask is 0xFF when bit i of m16 is set: each
-        // nibble spread to one bit per byte, then a byte permute whose
-        // selector 12 gives 0x00 and 13 gives 0xFF (no 32-bit multiply)
-        const u32x4 nib = {m16 & 15u, (m16 >> 4) & 15u, (m16 >> 8) & 15u, (m16 >> 12) & 15u};
-        const u32x4 sel = ((nib * 0x00204081u) & 0x01010101u) | 0x0C0C0C0Cu;
-        const u32x4 bm = {__builtin_amdgcn_perm(0u, 0u, sel.x), __builtin_amdgcn_perm(0u, 0u, sel.y),
-                          __builtin_amdgcn_perm(0u, 0u, sel.z), __builtin_amdgcn_perm(0u, 0u, sel.w)};
-        val = (val & ~bm) | (e & bm);
+        val |= e & sh.below[x1 - 16 * c] & ~sh.below[x0 - 16 * c];
         lit16 |= m16;
         if (sh.runend[r] >= d1) break;
       }
@@ -878,11 +933,15 @@ __global__ __launch_bounds__(kParseThreads, 6) void k_parse(ParseArgs a) {
       }
     }
     __syncthreads();
+    if (t < kMaxB / 64) sh.runbits[t] = 0;  // the next chunk's bits are set several barriers on
     dst += uint32_t(ptot & 0xFFFFFFFFu);
     litp += chunk_lit;
     ntok += n_tokc;
     for (int k = 0; k < 4; ++k) hist[k] = nh[k];
   }
+  // bytes taken of a staged stream
+  if (off_lds) offc = offc <= off_n ? (offc ? sh.offend[offc - 1] : 0u) : ~0u;
+  if (len_lds) lenc = lenc <= len_n ? (lenc ? sh.lenend[lenc - 1] : 0u) : ~0u;
   if (!failed && (dst != blen || litp != n_lit || lenc != n_len || offc != n_off || ntok != tok_n)) failed = true;
   if (failed) {
     if (t == 0) report(a.st, AX_E_CORRUPT, b);

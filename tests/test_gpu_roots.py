@@ -118,3 +118,33 @@ def test_batch_of_all(archives):
     assert batch.status()[0] == 0
     for name, x, o in zip(SHAPES, xs, outs):
         assert np.array_equal(o.cpu().numpy(), x), name
+
+
+@pytest.mark.parametrize("n_off", [15, 16, 17, 3071, 3072, 3073])
+@pytest.mark.parametrize("wide", [False, True])
+def test_offset_streams_around_the_stage(n_off, wide):
+    """A block whose offset stream has n_off bytes, of one-byte values or (wide)
+    of one- and two-byte ones, around a 16-byte piece and around what the parse
+    keeps in LDS; decoded matches against the oracle's parse."""
+    B = 16384
+    rng = np.random.default_rng(n_off)
+    x = rng.integers(0, 256, 2 * B).astype(np.uint8)
+    rows, p, used = [(0, 0, B, 0, 0)], B, 0
+    while used < n_off:
+        two = wide and n_off - used >= 2 and rng.random() < 0.5
+        src = int(rng.integers(128, B - 8)) if two else int(rng.integers(0, 120))
+        x[p: p + 4] = x[src: src + 4]
+        rows.append((1, p, 4, src, 0))
+        p, used = p + 4, used + (2 if two else 1)
+    rows.append((0, p, 2 * B - p, 0, 0))
+    arc = oracle.assemble(x, rows)
+    assert np.array_equal(oracle.decode(arc), x)
+    assert oracle.block_streams(arc, 1)["off"].size == n_off
+    dec = ax.Decoder(arc, torch.from_numpy(arc).cuda())
+    _say("offset stream", n_off, wide)
+    out = dec.decode_all()
+    assert dec.status()[0] == 0
+    assert np.array_equal(out.cpu().numpy(), x)
+    dec.build_index()
+    src, dst, ln = dec.tokens(0, len(rows) - 2)
+    assert [(int(a), int(b), int(c)) for a, b, c in zip(src, dst, ln)] == [(r[3], r[1], r[2]) for r in rows[1:-1]]
