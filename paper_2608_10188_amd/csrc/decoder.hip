@@ -2514,7 +2514,8 @@ __device__ inline void tile_or(uint32_t* tile, uint32_t at, B16 v) {
 // One workgroup per window block.  A token's first min(len, dist) bytes are
 // cut into items of kRootItem bytes, laid end to end over the wave's lanes;
 // the rest of a self-overlapping token repeats them (periodic fill) from the
-// tile.  The tile starts zeroed and the parse left zeros where matches go, so
+// tile.  (With five, six or eight waves a block the decode of 254 MB DNA takes
+// 790 to 804 us instead of 724.)  The tile starts zeroed and the parse left zeros where matches go, so
 // a 16-byte chunk of the block is finished by OR-ing the tile into it, and
 // chunks without match bytes are not touched.
 template <class O>
@@ -2524,14 +2525,23 @@ __global__ __launch_bounds__(kCopyThreads, 8) void k_roots(RootArgs a) {
   __shared__ uint32_t heads[kCopyThreads];                               // per wave: tokens starting at an item
   const uint32_t lane = lane_id(), item = a.first + xcd_item(blockIdx.x, gridDim.x);
   const WinBlock wb = a.wbl[item];
+  const uint32_t t1 = item + 1 < a.n_items ? a.wbl[item + 1].tok : a.n_tok;
+  const AX_GLOBAL u64x2* const tok = reinterpret_cast<const AX_GLOBAL u64x2*>(gp(a.tok));
+  // the block's tokens in as few passes as hold them, evenly over the waves of
+  // each, so that a wave's items mostly fit its lanes; the first pass's are
+  // loaded ahead
+  constexpr uint32_t kWaves = kCopyThreads / 64;
+  const uint32_t ntb = t1 - wb.tok, passes = (ntb + kCopyThreads - 1) / kCopyThreads;
+  const uint32_t share = passes ? (ntb + kWaves * passes - 1) / (kWaves * passes) : 0u;  // <= 64
+  const uint32_t base0 = wb.tok + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * share;
+  u64x2 tk = {0, 0};
+  if (lane < share && base0 + lane < t1) tk = tok[base0 + lane];
   const JobDev& J = a.jobs[wb.job];
   const typename RootWin<O>::type win(a, J, wb);
   const uint32_t B = J.B, sw = 1u << (a.s_log2 - 6);
   const uint64_t bs = wb.b * B;
   const gbytes ob = O(J).at(bs);
   const uint32_t blen = uint32_t(min<uint64_t>(B, J.n_bytes - bs));
-  const uint32_t t1 = item + 1 < a.n_items ? a.wbl[item + 1].tok : a.n_tok;
-  const AX_GLOBAL uint64_t* const tok = gp(a.tok);
   AX_GLOBAL uint32_t* const jarr = gp(a.J);
   uint8_t* const tile8 = reinterpret_cast<uint8_t*>(tile);
   uint32_t* const row32 = reinterpret_cast<uint32_t*>(row);
@@ -2544,19 +2554,15 @@ __global__ __launch_bounds__(kCopyThreads, 8) void k_roots(RootArgs a) {
   __syncthreads();
   bool wpend = false;  // this wave left bytes pending
   const uint32_t jblk = item << a.s_log2;  // window position of the block's first byte
-  for (uint32_t base = wb.tok + (threadIdx.x & ~63u); base < t1; base += kCopyThreads) {
-    const uint32_t t = base + lane;
-    const bool have = t < t1;
-    uint64_t tsrc = 0;
-    uint32_t trel = 0, tlen = 0, tn = 0;
-    if (have) {
-      tsrc = tok[2 * uint64_t(t)];
-      const uint64_t w = tok[2 * uint64_t(t) + 1], dst = w & ((1ull << 48) - 1);
-      tlen = uint32_t(w >> 48) + 1;
-      trel = uint32_t(dst - bs);
-      const uint64_t dist = dst - tsrc;
-      tn = dist < tlen ? uint32_t(dist) : tlen;
+  for (uint32_t base = base0; base < t1; base += kWaves * share) {
+    const bool have = lane < share && base + lane < t1;
+    if (base != base0) {
+      tk = u64x2{0, 0};
+      if (have) tk = tok[base + lane];
     }
+    const uint64_t tsrc = tk.x, dst = tk.y & ((1ull << 48) - 1), dist = dst - tsrc;
+    const uint32_t tlen = have ? uint32_t(tk.y >> 48) + 1 : 0u, trel = uint32_t(dst - bs);
+    const uint32_t tn = dist < tlen ? uint32_t(dist) : tlen;
     const uint32_t mine = (tn + kRootItem - 1) / kRootItem;
     const uint32_t incl = wave_incl_sum32(mine), start = incl - mine;
     const uint32_t total = __builtin_amdgcn_readlane(incl, 63);
@@ -2625,17 +2631,22 @@ __global__ __launch_bounds__(kCopyThreads, 8) void k_roots(RootArgs a) {
     }
   }
   const int any = __syncthreads_or(int(wpend));
-  const uint32_t full = blen / 16, nchunk = (blen + 15) / 16;
-  for (uint32_t c = threadIdx.x; c < nchunk; c += kCopyThreads) {
-    const u32x4 x = *reinterpret_cast<const u32x4*>(tile + 4 * c);
-    if (!(x.x | x.y | x.z | x.w)) continue;
-    if (c < full) {
-      AX_GLOBAL u32x4* const p = reinterpret_cast<AX_GLOBAL u32x4*>(ob + 16 * c);
-      *p = *p | x;
-    } else {
-      for (uint32_t i = 16 * c; i < blen; ++i) ob[i] |= tile8[i];
-    }
+  const uint32_t full = blen / 16;
+  constexpr uint32_t kChunks = kMaxB / 16 / kCopyThreads;  // a thread's, their loads in flight together
+  u32x4 add[kChunks], old[kChunks];
+#pragma unroll
+  for (uint32_t q = 0; q < kChunks; ++q) {
+    const uint32_t c = q * kCopyThreads + threadIdx.x;
+    add[q] = *reinterpret_cast<const u32x4*>(tile + 4 * c);
+    if (c >= full) add[q] = u32x4{0, 0, 0, 0};
+    old[q] = u32x4{0, 0, 0, 0};
+    if (add[q].x | add[q].y | add[q].z | add[q].w) old[q] = *reinterpret_cast<const AX_GLOBAL u32x4*>(ob + 16 * c);
   }
+#pragma unroll
+  for (uint32_t q = 0; q < kChunks; ++q)
+    if (add[q].x | add[q].y | add[q].z | add[q].w)
+      *reinterpret_cast<AX_GLOBAL u32x4*>(ob + 16 * (q * kCopyThreads + threadIdx.x)) = old[q] | add[q];
+  if (16 * full + threadIdx.x < blen) ob[16 * full + threadIdx.x] |= tile8[16 * full + threadIdx.x];  // the last bytes
   if (threadIdx.x < sw) gp(a.lmap)[uint64_t(item) * sw + threadIdx.x] = threadIdx.x < kMaxB / 64 ? row[threadIdx.x] : 0ull;
   if (any && threadIdx.x == 0) a.st->n_pending = 1;
 }
@@ -2725,7 +2736,11 @@ __global__ __launch_bounds__(kCopyThreads) void k_mark(RootArgs a) {
 constexpr uint32_t kXcds = 8;
 constexpr uint32_t kSweepSlots = 4;    // bytes a lane follows at a time
 constexpr uint32_t kSweepRows = 8;     // map words a wave follows at a time where every byte has an entry
-constexpr uint32_t kSweepChunk = 8;    // consecutive map words a wave takes at a time
+// Consecutive map words a wave takes at a time: rows of whole words where every
+// byte has an entry (80 MiB text with 8 / 4 / 2: 733 / 778 / 804 us), fewer
+// where pending bytes come in clusters (254 MB DNA 718 / 711 / 711 us, 16 MiB
+// in 4 KiB blocks 166 / 161 / 155 us).
+constexpr uint32_t kAllChunk = 8, kFewChunk = 4;
 constexpr uint32_t kSweepGrid = 2048;  // workgroups of a sweep or finish launch
 constexpr uint32_t kFinishWords = 8;   // map words a wave of k_finish has in flight
 constexpr uint32_t kFinishLimit = 1u << 24;  // hops k_finish follows before it reports a device error
@@ -2760,8 +2775,9 @@ struct WordQueue {
   uint32_t g[64];
 };
 
-// The map words [w0, w0 + n), `waves` waves taking kSweepChunk words in turn:
+// The map words [w0, w0 + n), `waves` waves taking kSweepChunk words each in turn:
 // step i of wave `wave` reads its next 64 words (64 / kSweepChunk chunks).
+template <uint32_t kSweepChunk>
 __device__ inline uint32_t queue_words(const uint64_t* lmap, uint64_t w0, uint64_t n, uint64_t wave, uint64_t waves,
                                        uint64_t i, WordQueue& q) {
   const uint32_t lane = lane_id();
@@ -2796,7 +2812,7 @@ __global__ __launch_bounds__(kCopyThreads) void k_sweep(SweepArgs a) {
   const uint64_t waves = uint64_t(gridDim.x / kXcds) * (kCopyThreads / 64);
   const uint64_t n = uint64_t(b1 - b0) << wl;
   for (uint64_t i = 0; i * 64 * waves < n; ++i) {
-    const uint32_t cnt = queue_words(a.lmap, uint64_t(b0) << wl, n, wave, waves, i, q);
+    const uint32_t cnt = queue_words<kAll ? kAllChunk : kFewChunk>(a.lmap, uint64_t(b0) << wl, n, wave, waves, i, q);
     if (kAll) {  // word by word: the bytes of a group of words leave as whole rows
       for (uint32_t c = 0; c < cnt; c += kSweepRows) {
         uint32_t v[kSweepRows], was[kSweepRows];
@@ -2877,7 +2893,7 @@ __global__ __launch_bounds__(kCopyThreads) void k_finish(SweepArgs a) {
   const uint64_t n = uint64_t(a.b1 - a.b0) << wl;
   const uint32_t sub = lane >> 4, q4 = 4 * (lane & 15u);
   for (uint64_t i = 0; i * 64 * waves < n; ++i) {
-    const uint32_t cnt = queue_words(a.lmap, uint64_t(a.b0) << wl, n, wave, waves, i, q);
+    const uint32_t cnt = queue_words<kAll ? kAllChunk : kFewChunk>(a.lmap, uint64_t(a.b0) << wl, n, wave, waves, i, q);
     for (uint32_t c = 0; c < cnt; c += kFinishWords) {
       constexpr uint32_t kRows = kFinishWords / 4;  // a lane's groups: word c + 4 h + lane / 16
       uint32_t bits[kRows], p[kRows];
@@ -3667,7 +3683,7 @@ static void enqueue_roots(Plan* P, const Plan::Win& W, const WinBlock* wbl, uint
   auto resolve = [&](uint32_t b0, uint32_t b1, bool all) {
     if (b0 == b1) return;
     // a wave per chunk of map words
-    const uint64_t waves = (uint64_t(b1 - b0) << (s_log2 - 6)) / kSweepChunk;
+    const uint64_t waves = (uint64_t(b1 - b0) << (s_log2 - 6)) / (all ? kAllChunk : kFewChunk);
     const uint32_t grid = std::max(1u, uint32_t(std::min<uint64_t>((waves + 3) / 4, kSweepGrid)));
     const dim3 sgrid((grid + kXcds - 1) / kXcds * kXcds);
     sa.b0 = b0, sa.b1 = b1, sa.settled = 0;
