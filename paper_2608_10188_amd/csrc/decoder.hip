@@ -197,13 +197,37 @@ __device__ inline uint32_t wave_excl_sum(uint32_t v, uint32_t* total) {
   return x - v;
 }
 
+// Wave-level moves for the scans (DPP): row_shr:k moves each lane's value k
+// lanes up inside its row of 16; row_bcast:15 / :31 hand lane 15 / 31 to the
+// rows selected by the row mask.  Lanes without a source, or in unselected
+// rows, receive `id`.
+constexpr int kDppRowShr = 0x110, kDppRowBcast15 = 0x142, kDppRowBcast31 = 0x143, kDppWaveShr1 = 0x138;
+template <int CTRL, int ROWS>
+__device__ inline uint32_t dpp_move(uint32_t id, uint32_t x) {
+  return uint32_t(__builtin_amdgcn_update_dpp(int(id), int(x), CTRL, ROWS, 0xF, false));
+}
+
+// Inclusive wave scan of a u32 (sum): 1, 2, 4, 8 inside the rows, then the
+// row totals across rows.
+__device__ inline uint32_t wave_incl_sum32(uint32_t x) {
+  x += dpp_move<kDppRowShr + 1, 0xF>(0, x);
+  x += dpp_move<kDppRowShr + 2, 0xF>(0, x);
+  x += dpp_move<kDppRowShr + 4, 0xF>(0, x);
+  x += dpp_move<kDppRowShr + 8, 0xF>(0, x);
+  x += dpp_move<kDppRowBcast15, 0xA>(0, x);
+  x += dpp_move<kDppRowBcast31, 0xC>(0, x);
+  return x;
+}
+
+// The decode loop is a chain of three LDS reads per symbol and is bound by
+// instruction issue when the device is full, by that chain when it is not.
+// Tables go by a symbol's rank among the present ones: the slot table is then
+// a prefix sum over start marks, four slots a word, instead of a loop over the
+// slots and the symbol list.
 __global__ __launch_bounds__(64) void k_ans(AnsArgs a) {
-  __shared__ __attribute__((aligned(16))) uint8_t symtab[ax::kProbScale];
-  // f | cum << 16 indexed by symbol; while the slot table is filled, the same
-  // bytes hold the cum (sentinel 4096) and the symbol of the k-th present one
-  __shared__ __attribute__((aligned(16))) uint32_t fctab[256];
-  uint16_t* const cumtab = reinterpret_cast<uint16_t*>(fctab);         // 257 entries
-  uint8_t* const symlist = reinterpret_cast<uint8_t*>(fctab) + 2 * 260;  // 256 entries
+  // slot -> rank, or 4 * rank (the entry's place in bytes) where that fits
+  __shared__ __attribute__((aligned(16))) uint8_t ranktab[ax::kProbScale];
+  __shared__ uint32_t fctab[256];  // by rank: f | cum << 12 | symbol << 24
 
   const uint32_t item = blockIdx.x % a.n_items;
   const uint32_t stream = blockIdx.x / a.n_items;  // 0 LIT, 1 LEN, 2 OFF, 3 CMD
@@ -271,70 +295,63 @@ __global__ __launch_bounds__(64) void k_ans(AnsArgs a) {
     if (lane == 0) { report(a.st, AX_E_CORRUPT, b); *nsym = 0; }
     return;
   }
-  // --- table: lane l holds up to four present symbols in ascending order.
-  uint32_t mysym[4], myf[4], cnt = 0;
+  // --- tables: lane l holds up to four present symbols in ascending order.
+  uint32_t sym0 = 4 * lane, bits = 0;  // its symbols: sym0 + j where bit j is set
   if (present <= 32) {
-    if (lane < present) { mysym[0] = rec[set_at + lane]; cnt = 1; }
+    if (lane < present) sym0 = rec[set_at + lane], bits = 1;
   } else {
-    const uint32_t bits = (rec[set_at + (lane >> 1)] >> ((lane & 1) * 4)) & 15u;
-    for (uint32_t j = 0; j < 4; ++j)
-      if (bits >> j & 1) mysym[cnt++] = lane * 4 + j;
+    bits = (rec[set_at + (lane >> 1)] >> ((lane & 1) * 4)) & 15u;
   }
-  uint32_t total_present;
-  const uint32_t rank0 = wave_excl_sum(cnt, &total_present);
-  uint32_t fsum = 0;
-  bad = total_present != present;
-  for (uint32_t j = 0; j < cnt; ++j) {
-    myf[j] = (rank0 + j < present) ? *reinterpret_cast<const uint16_t*>(rec + freq_at + 2 * (rank0 + j)) : 0;
+  const uint32_t cnt = __popc(bits), ranks = wave_incl_sum32(cnt), rank0 = ranks - cnt;
+  bad = uint32_t(__builtin_amdgcn_readlane(ranks, 63)) != present;
+  uint32_t myf[4], fsum = 0;
+#pragma unroll
+  for (uint32_t j = 0, r = rank0; j < 4; ++j) {
+    myf[j] = 0;
+    if (!((bits >> j) & 1)) continue;
+    if (r < present) myf[j] = *reinterpret_cast<const uint16_t*>(rec + freq_at + 2 * r);
     bad |= myf[j] < 1 || myf[j] >= ax::kProbScale;
     fsum += myf[j];
+    ++r;
   }
-  if (present <= 32 && cnt && lane > 0) bad |= rec[set_at + lane - 1] >= mysym[0];  // strictly ascending
-  uint32_t ftotal;
-  uint32_t cum = wave_excl_sum(fsum, &ftotal);
-  bad |= ftotal != ax::kProbScale;
+  if (present <= 32 && cnt && lane > 0) bad |= rec[set_at + lane - 1] >= sym0;  // strictly ascending
+  const uint32_t fincl = wave_incl_sum32(fsum);
+  bad |= uint32_t(__builtin_amdgcn_readlane(fincl, 63)) != ax::kProbScale;
+  const u32x4 zero = {0, 0, 0, 0};
+#pragma unroll
+  for (uint32_t q = 0; q < 4; ++q) *reinterpret_cast<u32x4*>(ranktab + 64 * lane + 16 * q) = zero;
   if (__ballot(bad)) {
     if (lane == 0) { report(a.st, AX_E_CORRUPT, b); *nsym = 0; }
     return;
   }
-  {
-    uint32_t c = cum;
-    for (uint32_t j = 0; j < cnt; ++j) {
-      cumtab[rank0 + j] = uint16_t(c);
-      symlist[rank0 + j] = uint8_t(mysym[j]);
-      c += myf[j];
-    }
-  }
-  if (lane == 0) cumtab[present] = ax::kProbScale;
   __syncthreads();
-  {  // slot -> symbol: lane l fills slots [64l, 64l+64) four at a time
-    const uint32_t s0 = lane * 64;
-    uint32_t lo = 0, hi = present - 1;  // last k with cumtab[k] <= s0
-    while (lo < hi) {
-      const uint32_t mid = (lo + hi + 1) >> 1;
-      if (cumtab[mid] <= s0) lo = mid; else hi = mid - 1;
-    }
-    uint32_t k = lo, next = cumtab[k + 1];
-    if (next >= s0 + 64) {  // one symbol owns all 64 slots: four 16-byte stores
-      const uint32_t rep = uint32_t(symlist[k]) * 0x01010101u;
-      const u32x4 v = {rep, rep, rep, rep};
 #pragma unroll
-      for (uint32_t q = 0; q < 4; ++q) *reinterpret_cast<u32x4*>(symtab + s0 + 16 * q) = v;
-    } else {
-      for (uint32_t s = s0; s < s0 + 64; s += 4) {
-        uint32_t packed = 0;
-        for (uint32_t q = 0; q < 4; ++q) {
-          while (s + q >= next) { ++k; next = cumtab[k + 1]; }
-          packed |= uint32_t(symlist[k]) << (8 * q);
-        }
-        *reinterpret_cast<uint32_t*>(symtab + s) = packed;
+  for (uint32_t j = 0, r = rank0, cum = fincl - fsum; j < 4; ++j) {  // cum < 4096: every f is at least 1
+    if (!((bits >> j) & 1)) continue;
+    fctab[r] = myf[j] | (cum << 12) | ((sym0 + j) << 24);
+    if (r) ranktab[cum] = present <= 64 ? 4 : 1;
+    cum += myf[j];
+    ++r;
+  }
+  __syncthreads();
+  {  // marks -> ranks: lane l sums its slots [64l, 64l+64), byte-wise four a word
+    u32x4 v[4];
+    uint32_t run = 0;  // the sum so far, in every byte
+#pragma unroll
+    for (uint32_t q = 0; q < 4; ++q) {
+      v[q] = *reinterpret_cast<const u32x4*>(ranktab + 64 * lane + 16 * q);
+#pragma unroll
+      for (uint32_t e = 0; e < 4; ++e) {
+        uint32_t x = v[q][e];
+        x += x << 8;
+        x += x << 16;
+        v[q][e] = x + run;
+        run = __builtin_amdgcn_perm(0u, v[q][e], 0x03030303u);
       }
     }
-  }
-  __syncthreads();
-  for (uint32_t j = 0; j < cnt; ++j) {  // now the frequency table (over the build's lists)
-    fctab[mysym[j]] = myf[j] | (cum << 16);
-    cum += myf[j];
+    const uint32_t mine = run & 0xFFu, base = (wave_incl_sum32(mine) - mine) * 0x01010101u;
+#pragma unroll
+    for (uint32_t q = 0; q < 4; ++q) *reinterpret_cast<u32x4*>(ranktab + 64 * lane + 16 * q) = v[q] + base;
   }
   __syncthreads();
   // --- decode: lane j owns symbols j, j+K, ...
@@ -359,8 +376,8 @@ __global__ __launch_bounds__(64) void k_ans(AnsArgs a) {
   // one step for the lanes in `need` (a subset of the decoding lanes):
   // returns the new state of a lane from its decoded xn
   auto renorm = [&](uint64_t m, uint32_t xn, bool need) -> uint32_t {
-    const uint32_t q = __builtin_amdgcn_mbcnt_hi(uint32_t(m >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(m), 0u)) +
-                       (ptr - base);  // < 128; the permute takes the lane mod 64
+    const uint32_t q = __builtin_amdgcn_mbcnt_hi(
+        uint32_t(m >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(m), ptr - base));  // < 128; the permute takes the lane mod 64
     const uint32_t v = __builtin_amdgcn_ds_bpermute(int(q << 2), int(P));
     // (xn << 16) | the word: xn's two low bytes above v's low or high half
     const uint32_t xr = __builtin_amdgcn_perm(xn, v, q < 64 ? 0x05040100u : 0x05040302u);
@@ -372,40 +389,69 @@ __global__ __launch_bounds__(64) void k_ans(AnsArgs a) {
     }
     return need ? xr : xn;
   };
-  // Steps with all K lanes decoding: no per-lane bounds; symbols leave
-  // through a buffer store addressed by the lane plus a wave-uniform offset.
-  // With K = 64 neither the ballot nor the store needs a lane mask
+  // Steps with all K lanes decoding: no per-lane bounds (a lane beyond K
+  // decodes its own state and stores past the buffer's end, which drops it;
+  // with K = 64 not even the ballot needs a mask).  Four steps' symbols are
+  // gathered in a register, transposed in groups of four lanes, and leave as
+  // one word per lane: a byte store for each step kept the store path busy for
+  // three quarters of the kernel's time (254 MB DNA: 173 us, now 162; with the
+  // slot table filled slot by slot 181)
   const uint32_t full = n / K;
   const uint64_t kmask = K == 64 ? ~0ull : ((1ull << K) - 1ull);
   const __amdgpu_buffer_rsrc_t orsrc = __builtin_amdgcn_make_buffer_rsrc(outs[stream], 0, int(n), kBufferWord3);
-  auto full_steps = [&](auto all_tag) {
+  const uint32_t beyond = lane < K ? 0u : 0x40000000u;
+  auto entry = [&](auto small_tag, uint32_t slot) -> uint32_t {
+    const uint32_t r = ranktab[slot];
+    if (decltype(small_tag)::value) return *reinterpret_cast<const uint32_t*>(reinterpret_cast<const uint8_t*>(fctab) + r);
+    return fctab[r];
+  };
+  auto full_steps = [&](auto all_tag, auto small_tag) {
     constexpr bool kAll = decltype(all_tag)::value;
-    for (uint32_t t = 0; t < full; ++t) {
+    auto step = [&]() -> uint32_t {
       const uint32_t slot = x & (ax::kProbScale - 1);
-      const uint32_t s = symtab[slot];
-      const uint32_t fc = fctab[s];
-      const uint32_t xn = (fc & 0xFFFFu) * (x >> ax::kProbBits) + slot - (fc >> 16);
+      const uint32_t fc = entry(small_tag, slot);
+      const uint32_t xn = (fc & 0xFFFu) * (x >> ax::kProbBits) + slot - ((fc >> 12) & 0xFFFu);
       const bool need = xn < ax::kRansLow;
       uint64_t m = __builtin_amdgcn_ballot_w64(need);
       if (!kAll) m &= kmask;
-      if (kAll || lane < K) __builtin_amdgcn_raw_buffer_store_b8(uint8_t(s), orsrc, int(lane), int(t * K), 0);
       x = renorm(m, xn, need);
+      return fc;
+    };
+    uint32_t t = 0;
+    if (kAll || K >= 4) {
+      // lane 4 q + i takes step i's symbols of lanes 4 q .. 4 q + 3
+      const uint32_t sel1 = lane & 1 ? 0x03070105u : 0x06020400u, sel2 = lane & 2 ? 0x03020706u : 0x05040100u;
+      const int at = int(((lane & 3u) * K + (lane & ~3u)) | beyond);
+      for (; t + 4 <= full; t += 4) {
+        uint32_t v = 0;
+#pragma unroll
+        for (uint32_t q = 0; q < 4; ++q) v = __builtin_amdgcn_perm(step(), v, 0x07030201u);  // symbols are the top bytes
+        v = __builtin_amdgcn_perm(dpp_move<0xB1, 0xF>(0, v), v, sel1);  // with lane ^ 1
+        v = __builtin_amdgcn_perm(dpp_move<0x4E, 0xF>(0, v), v, sel2);  // with lane ^ 2
+        __builtin_amdgcn_raw_buffer_store_b32(v, orsrc, at, int(t * K), 0);
+      }
+    }
+    for (; t < full; ++t) {
+      const uint32_t fc = step();
+      __builtin_amdgcn_raw_buffer_store_b8(uint8_t(fc >> 24), orsrc, int(lane | beyond), int(t * K), 0);
     }
   };
-  if (K == 64) full_steps(std::true_type{});
-  else full_steps(std::false_type{});
+  const bool small = present <= 64;
+  if (K == 64 && small) full_steps(std::true_type{}, std::true_type{});
+  else if (K == 64) full_steps(std::true_type{}, std::false_type{});
+  else if (small) full_steps(std::false_type{}, std::true_type{});
+  else full_steps(std::false_type{}, std::false_type{});
   uint32_t i = full * K + lane;
   for (uint32_t t = full; t < steps; ++t, i += K) {
     const bool act = lane < K && i < n;
     const uint32_t slot = x & (ax::kProbScale - 1);
-    const uint32_t s = symtab[slot];
-    const uint32_t fc = fctab[s];
-    const uint32_t xn = (fc & 0xFFFFu) * (x >> ax::kProbBits) + slot - (fc >> 16);
+    const uint32_t fc = small ? entry(std::true_type{}, slot) : entry(std::false_type{}, slot);
+    const uint32_t xn = (fc & 0xFFFu) * (x >> ax::kProbBits) + slot - ((fc >> 12) & 0xFFFu);
     const bool need = act && xn < ax::kRansLow;
     const uint32_t xr = renorm(__ballot(need), xn, need);
     if (act) {
       x = xr;
-      out[i] = uint8_t(s);
+      out[i] = uint8_t(fc >> 24);
     }
   }
   bad |= lane < K && x != ax::kRansLow;
@@ -509,28 +555,6 @@ __device__ inline bool block_any(bool p, ParseShared& sh, int k) {
   if (lane_id() == 0) sh.anyb[k][threadIdx.x >> 6] = uint8_t(w);
   __syncthreads();
   return *reinterpret_cast<const uint32_t*>(sh.anyb[k]) != 0;
-}
-
-// Wave-level moves for the scans (DPP): row_shr:k moves each lane's value k
-// lanes up inside its row of 16; row_bcast:15 / :31 hand lane 15 / 31 to the
-// rows selected by the row mask.  Lanes without a source, or in unselected
-// rows, receive `id`.
-constexpr int kDppRowShr = 0x110, kDppRowBcast15 = 0x142, kDppRowBcast31 = 0x143, kDppWaveShr1 = 0x138;
-template <int CTRL, int ROWS>
-__device__ inline uint32_t dpp_move(uint32_t id, uint32_t x) {
-  return uint32_t(__builtin_amdgcn_update_dpp(int(id), int(x), CTRL, ROWS, 0xF, false));
-}
-
-// Inclusive wave scan of a u32 (sum): 1, 2, 4, 8 inside the rows, then the
-// row totals across rows.
-__device__ inline uint32_t wave_incl_sum32(uint32_t x) {
-  x += dpp_move<kDppRowShr + 1, 0xF>(0, x);
-  x += dpp_move<kDppRowShr + 2, 0xF>(0, x);
-  x += dpp_move<kDppRowShr + 4, 0xF>(0, x);
-  x += dpp_move<kDppRowShr + 8, 0xF>(0, x);
-  x += dpp_move<kDppRowBcast15, 0xA>(0, x);
-  x += dpp_move<kDppRowBcast31, 0xC>(0, x);
-  return x;
 }
 
 // Block-wide exclusive scan of a u64 holding two u32 sums (the halves are
