@@ -2701,23 +2701,29 @@ __global__ __launch_bounds__(kCopyThreads) void k_mark(RootArgs a) {
   const AX_GLOBAL u32x4* const rec = block_recs(a.cmd, 1u << a.s_log2, item);
   AX_GLOBAL uint32_t* const je = gp(a.J) + (uint64_t(item) << a.s_log2);
   if (__hip_atomic_load(&a.st->err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) return;
-  for (uint32_t p = p0 + 4 * threadIdx.x; p < min(blen, p0 + (1u << a.mark_log2)); p += 4 * kCopyThreads) {
+  const uint32_t end = min(blen, p0 + (1u << a.mark_log2));
+  // (two and four groups of four positions a thread with their loads in flight
+  // together take registers from resident waves: 80 MiB text 676 -> 689, 723 us)
+  for (uint32_t p = p0 + 4 * threadIdx.x; p < end; p += 4 * kCopyThreads) {
     const u32x4 q = rec[p >> 5];
-    const uint32_t bit = p & 31u, cov = (q.x >> bit) & 0xFu;
+    const uint32_t bit = p & 31u, cov = (q.x >> bit) & 0xFu, starts = q.y >> bit;
     uint32_t lit = 0;
-    if (cov != 0xFu) {
-      if (p + 4 <= blen) lit = *reinterpret_cast<const AX_GLOBAL uint32_t*>(ob + p);
-      else
-        for (uint32_t e = 0; p + e < blen; ++e) lit |= uint32_t(ob[p + e]) << (8 * e);
-    }
-    uint32_t u = q.z + uint32_t(__popc(q.y & (~0u >> (31 - bit)))) - 1;  // the match of byte 0, if it has one
-    const uint32_t starts = q.y >> bit;
-    u64x2 t = {0, 0};
+    if (p + 4 <= blen) lit = *reinterpret_cast<const AX_GLOBAL uint32_t*>(ob + p);
+    else
+      for (uint32_t e = 0; p + e < blen; ++e) lit |= uint32_t(ob[p + e]) << (8 * e);
+    // the match of byte 0, if it has one, and the next one to start, loaded together
+    uint32_t u = q.z + uint32_t(__popc(q.y & (~0u >> (31 - bit)))) - 1;
+    u64x2 t = {0, 0}, t2 = {0, 0};
     if (cov & 1u) t = tok[u];
+    if (starts & 0xEu) t2 = tok[u + 1];
     u32x4 v;
 #pragma unroll
     for (uint32_t e = 0; e < 4; ++e) {
-      if (e && ((starts >> e) & 1u)) t = tok[++u];
+      if (e && ((starts >> e) & 1u)) {
+        t = t2;
+        ++u;
+        if (starts & (0xEu << e) & 0xFu) t2 = tok[u + 1];  // matches shorter than four bytes
+      }
       uint32_t x = kJRes | ((lit >> (8 * e)) & 0xFFu);
       if ((cov >> e) & 1u) {
         const uint64_t ud = t.y & ((1ull << 48) - 1), dist = ud - t.x;
@@ -2766,7 +2772,7 @@ constexpr uint32_t kSweepRows = 8;     // map words a wave follows at a time whe
 // in 4 KiB blocks 166 / 161 / 155 us).
 constexpr uint32_t kAllChunk = 8, kFewChunk = 4;
 constexpr uint32_t kSweepGrid = 2048;  // workgroups of a sweep or finish launch
-constexpr uint32_t kFinishWords = 8;   // map words a wave of k_finish has in flight
+constexpr uint32_t kFinishWords = 4;   // map words a wave of k_finish has in flight (80 MiB text with 8: 701, not 677 us)
 constexpr uint32_t kFinishLimit = 1u << 24;  // hops k_finish follows before it reports a device error
 
 struct SweepArgs {
