@@ -687,7 +687,7 @@ __device__ bool leb_values(Src src, uint32_t n, uint32_t* cursor, uint32_t count
 }
 
 // The terminators (bytes below 0x80) among the first n bytes of v, one bit per byte.
-__device__ inline uint32_t leb_ends(uint4 v, uint32_t n) {
+__device__ inline uint32_t leb_ends(u32x4 v, uint32_t n) {
   auto four = [](uint32_t w) {
     w = (~w >> 7) & 0x01010101u;
     return (w | (w >> 7) | (w >> 14) | (w >> 21)) & 0xFu;
@@ -728,48 +728,49 @@ template <class O, bool kRecs>
 __global__ __launch_bounds__(kParseThreads, 7) void k_parse(ParseArgs a) {
   __shared__ ParseShared sh;
   const uint32_t item = blockIdx.x, t = threadIdx.x;
+  const uint8_t* cmd = a.cmd + uint64_t(item) * a.slot_b;
+  const AX_GLOBAL uint8_t* const litg = gp(a.lit + uint64_t(item) * a.slot_b);
+  const uint8_t* offs = a.off + uint64_t(item) * a.off_cap;
+  const uint8_t* lens = a.len + uint64_t(item) * a.len_cap;
+  // loads that need only the block's place in the window come first: the
+  // chunk's command bytes (inside the slot whatever the count: kParseThreads
+  // <= slot_b) and one 16-byte piece per thread of the offset and length
+  // streams, staged in LDS if the stream fits the stage (the slots are
+  // 16-aligned and their capacities multiples of 16, so the loads stay in this
+  // block's slots)
+  static_assert(kOffStage <= 16 * kParseThreads && kLenStage <= 16 * kParseThreads, "one piece per thread");
+  uint32_t cnext = gp(cmd)[t];
+  u32x4 po = {0, 0, 0, 0}, pl = {0, 0, 0, 0};
+  if (16 * t < min(kOffStage, a.off_cap)) po = *reinterpret_cast<const AX_GLOBAL u32x4*>(gp(offs) + 16 * t);
+  if (16 * t < min(kLenStage, a.len_cap)) pl = *reinterpret_cast<const AX_GLOBAL u32x4*>(gp(lens) + 16 * t);
   const WinBlock wb = a.wbl[item];
+  const uint64_t tok_lo = wb.tok, tok_n = (item + 1 < a.n_items ? a.wbl[item + 1].tok : a.n_tok) - wb.tok;
+  const uint32_t n_lit = a.nsym[4 * item + 0], n_len = a.nsym[4 * item + 1];
+  const uint32_t n_off = a.nsym[4 * item + 2], n_cmd = a.nsym[4 * item + 3];
   const JobDev& J = a.jobs[wb.job];
   const uint64_t b = wb.b;
   const uint32_t B = J.B, mm = J.mm;
   const uint64_t bs = b * B;
   const uint32_t blen = uint32_t(min<uint64_t>(B, J.n_bytes - bs));
-  const uint32_t n_lit = a.nsym[4 * item + 0], n_len = a.nsym[4 * item + 1];
-  const uint32_t n_off = a.nsym[4 * item + 2], n_cmd = a.nsym[4 * item + 3];
-  const uint8_t* cmd = a.cmd + uint64_t(item) * a.slot_b;
-  const AX_GLOBAL uint8_t* const litg = gp(a.lit + uint64_t(item) * a.slot_b);
-  const uint8_t* offs = a.off + uint64_t(item) * a.off_cap;
-  const uint8_t* lens = a.len + uint64_t(item) * a.len_cap;
+  // the archive's own match count, checked at the end
   const uint64_t* mpre = reinterpret_cast<const uint64_t*>(J.arc + 64) + J.nb + 1;
-  const uint64_t tok_lo = wb.tok, tok_n = mpre[b + 1] - mpre[b];
+  const uint64_t arc_n = mpre[b + 1] - mpre[b];
 
   if (t == 0)
-    sh.bad = (n_lit > B || n_cmd > B || n_len > job_len_cap(J) || n_off > job_off_cap(J) ||
-              tok_lo + tok_n > a.n_tok) ? 1 : 0;
+    sh.bad = (n_lit > B || n_cmd > B || n_len > job_len_cap(J) || n_off > job_off_cap(J)) ? 1 : 0;
   if (kRecs && t < kMaxB / 64) sh.covw[t] = 0, sh.startw[t] = 0;
   static_assert(kMaxB / 64 <= kParseThreads, "one map word per thread");
   // the block's output bytes (contiguous); groups below `full` are whole
   AX_GLOBAL uint8_t* const o = a.write_out ? O(J).at(bs) : nullptr;
   const uint32_t full = blen & ~15u;
-  // the first chunk's command bytes, loaded ahead of the staging barrier
-  // (inside the slot whatever the count: kParseThreads <= slot_b)
-  uint32_t cnext = cmd[t];
-  // stage the offset and length streams in LDS: one 16-byte piece per
-  // thread, loaded before the stream lengths are known (the slots are
-  // 16-aligned and their capacities multiples of 16, so the loads stay in
-  // this block's slots) and kept if the stream fits the stage
-  static_assert(kOffStage <= 16 * kParseThreads && kLenStage <= 16 * kParseThreads, "one piece per thread");
-  uint4 po = {0, 0, 0, 0}, pl = {0, 0, 0, 0};
-  if (16 * t < min(kOffStage, a.off_cap)) po = *reinterpret_cast<const uint4*>(offs + 16 * t);
-  if (16 * t < min(kLenStage, a.len_cap)) pl = *reinterpret_cast<const uint4*>(lens + 16 * t);
   const bool off_lds = n_off <= kOffStage, len_lds = n_len <= kLenStage;
   uint32_t oe = 0, le = 0;
   if (off_lds && 16 * t < n_off) {
-    *reinterpret_cast<uint4*>(sh.offb + 16 * t) = po;
+    *reinterpret_cast<u32x4*>(sh.offb + 16 * t) = po;
     oe = leb_ends(po, n_off - 16 * t);
   }
   if (len_lds && 16 * t < n_len) {
-    *reinterpret_cast<uint4*>(sh.lenb + 16 * t) = pl;
+    *reinterpret_cast<u32x4*>(sh.lenb + 16 * t) = pl;
     le = leb_ends(pl, n_len - 16 * t);
   }
   if (t < 17) {
@@ -966,7 +967,8 @@ __global__ __launch_bounds__(kParseThreads, 7) void k_parse(ParseArgs a) {
   // bytes taken of a staged stream
   if (off_lds) offc = offc <= off_n ? (offc ? sh.offend[offc - 1] : 0u) : ~0u;
   if (len_lds) lenc = lenc <= len_n ? (lenc ? sh.lenend[lenc - 1] : 0u) : ~0u;
-  if (!failed && (dst != blen || litp != n_lit || lenc != n_len || offc != n_off || ntok != tok_n)) failed = true;
+  if (!failed && (dst != blen || litp != n_lit || lenc != n_len || offc != n_off || ntok != tok_n || arc_n != tok_n))
+    failed = true;
   if (failed) {
     if (t == 0) report(a.st, AX_E_CORRUPT, b);
     return;
