@@ -13,7 +13,7 @@
 #include <algorithm>
 #include <atomic>
 #include <cstring>
-#include <unordered_map>
+#include <memory>
 #include <new>
 #include <system_error>
 #include <thread>
@@ -26,36 +26,57 @@
 namespace {
 
 // Byte-precise set of needed output positions: one bitmap per touched block
-// (B bits), allocated from a pool.  Inserting a range reports the runs of
-// positions that were not needed before, which become new work.
+// (B bits), allocated from a pool and found through an open-addressing table.
+// Inserting a range reports the runs of positions that were not needed before,
+// which become new work.
 class NeedSet {
  public:
-  explicit NeedSet(uint64_t B) : B_(B), words_(B / 64) {}
+  explicit NeedSet(uint64_t B) : words_(B / 64), lb_(unsigned(__builtin_ctzll(B))), table_(64, kNone) {}
 
-  // Mark [a, b) needed; append to `fresh` the maximal runs newly marked.
+  // Mark [a, b) needed; append to `fresh` the maximal runs newly marked.  Most
+  // sources lie in what is needed already: within a block's two words that is
+  // one look at each.
   void insert(uint64_t a, uint64_t b, std::vector<std::pair<uint64_t, uint64_t>>& fresh) {
+    if (a >= b) return;
+    const uint64_t l = b - 1;
+    if (a >> lb_ == l >> lb_ && (l >> 6) - (a >> 6) <= 1) {
+      const uint64_t* const bm = bitmap(a >> lb_) + ((a >> 6) & (words_ - 1));
+      const uint64_t head = ~0ull << (a & 63), tail = ~0ull >> (63 - (l & 63));
+      if (a >> 6 == l >> 6 ? !(~bm[0] & head & tail) : !((~bm[0] & head) | (~bm[1] & tail))) return;
+    }
+    insert_fresh(a, b, fresh);
+  }
+
+ private:
+  void insert_fresh(uint64_t a, uint64_t b, std::vector<std::pair<uint64_t, uint64_t>>& fresh) {
     uint64_t run0 = 0;
     bool open = false;
     while (a < b) {
-      const uint64_t blk = a / B_, base = blk * B_, e = std::min(b, base + B_);
+      const uint64_t blk = a >> lb_, base = blk << lb_, e = std::min(b, base + (uint64_t(1) << lb_));
       uint64_t* bm = bitmap(blk);
       for (uint64_t p = a; p < e;) {
         const uint64_t w = (p - base) >> 6, bit = (p - base) & 63;
         const uint64_t n = std::min<uint64_t>(64 - bit, e - p);
         const uint64_t m = (n == 64 ? ~0ull : ((1ull << n) - 1)) << bit;
-        uint64_t nw = m & ~bm[w];
+        const uint64_t nw = m & ~bm[w];
         bm[w] |= m;
-        // walk the word's bits [bit, bit + n): runs of newly marked positions
-        uint64_t q = bit;
-        while (q < bit + n) {
-          const bool isnew = (nw >> q) & 1;
-          const uint64_t rest = isnew ? ~nw : nw;  // first position where the state flips
-          uint64_t flip = rest >> q ? q + __builtin_ctzll(rest >> q) : 64;
-          flip = std::min<uint64_t>(flip, bit + n);
-          const uint64_t pa = base + w * 64 + q;
-          if (isnew && !open) run0 = pa, open = true;
-          if (!isnew && open) fresh.emplace_back(run0, pa), open = false;
-          q = flip;
+        if (nw == m) {  // all new, or none: the common words
+          if (!open) run0 = p, open = true;
+        } else if (nw == 0) {
+          if (open) fresh.emplace_back(run0, p), open = false;
+        } else {
+          // walk the word's bits [bit, bit + n): runs of newly marked positions
+          uint64_t q = bit;
+          while (q < bit + n) {
+            const bool isnew = (nw >> q) & 1;
+            const uint64_t rest = isnew ? ~nw : nw;  // first position where the state flips
+            uint64_t flip = rest >> q ? q + __builtin_ctzll(rest >> q) : 64;
+            flip = std::min<uint64_t>(flip, bit + n);
+            const uint64_t pa = base + w * 64 + q;
+            if (isnew && !open) run0 = pa, open = true;
+            if (!isnew && open) fresh.emplace_back(run0, pa), open = false;
+            q = flip;
+          }
         }
         p += n;
       }
@@ -64,42 +85,94 @@ class NeedSet {
     if (open) fresh.emplace_back(run0, b);
   }
 
+ public:
   // Ascending list of touched blocks (appended to out).
   void blocks(std::vector<uint64_t>& out) const {
     const size_t at = out.size();
-    for (const auto& kv : slot_) out.push_back(kv.first);
+    out.insert(out.end(), blocks_.begin(), blocks_.end());
     std::sort(out.begin() + at, out.end());
   }
-  size_t count() const { return slot_.size(); }
 
  private:
+  static constexpr uint32_t kNone = 0xFFFFFFFFu, kChunk = 16;
+  size_t place(uint64_t blk) const { return size_t((blk * 0x9E3779B97F4A7C15ull) >> 32) & (table_.size() - 1); }
   uint64_t* bitmap(uint64_t blk) {
-    if (blk == last_blk_) return pool_.data() + last_at_;  // runs of lookups hit one block
-    auto it = slot_.find(blk);
-    if (it == slot_.end()) {
-      it = slot_.emplace(blk, pool_.size()).first;
-      pool_.resize(pool_.size() + words_, 0);
+    if (blk == last_blk_) return last_;  // runs of lookups hit one block
+    size_t h = place(blk);
+    while (table_[h] != kNone && blocks_[table_[h]] != blk) h = (h + 1) & (table_.size() - 1);
+    if (table_[h] == kNone) {
+      if (blocks_.size() % kChunk == 0) pool_.push_back(std::make_unique<uint64_t[]>(kChunk * words_));  // zeroed
+      blocks_.push_back(blk);
+      table_[h] = uint32_t(blocks_.size() - 1);
+      last_ = at(table_[h]);
+      if (2 * blocks_.size() > table_.size()) grow();
+    } else {
+      last_ = at(table_[h]);
     }
     last_blk_ = blk;
-    last_at_ = it->second;
-    return pool_.data() + it->second;
+    return last_;
   }
-  uint64_t B_, words_;
-  std::unordered_map<uint64_t, size_t> slot_;
-  std::vector<uint64_t> pool_;
+  uint64_t* at(uint32_t i) const { return pool_[i / kChunk].get() + (i % kChunk) * words_; }
+  void grow() {
+    table_.assign(2 * table_.size(), kNone);
+    for (uint32_t i = 0; i < blocks_.size(); ++i) {
+      size_t h = place(blocks_[i]);
+      while (table_[h] != kNone) h = (h + 1) & (table_.size() - 1);
+      table_[h] = i;
+    }
+  }
+  size_t words_;
+  unsigned lb_;
+  std::vector<uint32_t> table_;   // index into blocks_, or kNone
+  std::vector<uint64_t> blocks_;  // touched blocks, in the order of their bitmaps
+  std::vector<std::unique_ptr<uint64_t[]>> pool_;  // bitmaps, kChunk at a time (never moved)
   uint64_t last_blk_ = ~0ull;
-  size_t last_at_ = 0;
+  uint64_t* last_ = nullptr;
 };
 
 // Host threads for the closures of n ranges: one per 8 ranges when they are
 // short (a closure takes microseconds, starting a thread tens of them), one
-// per range of at least 64 KiB (its closure takes milliseconds), 16 at most
-// by default (the process may see more cores than its share).
+// per two ranges of at least 64 KiB (32 ranges of 16 KiB to 1 MiB: 1100 us on
+// one thread, 255 on 8, 240 on 10, 280 on 16), 16 at most by default (the
+// process may see more cores than its share).
 uint32_t closure_threads(uint32_t n, const uint64_t* lens, uint32_t threads) {
   uint32_t big = 0;
   for (uint32_t i = 0; i < n; ++i) big += lens[i] >= (64u << 10);
   const uint32_t cap = threads ? threads : std::min(16u, std::max(1u, std::thread::hardware_concurrency()));
-  return std::max(1u, std::min({cap, std::max((n + 7) / 8, big), 64u}));
+  return std::max(1u, std::min({cap, std::max((n + 7) / 8, (big + 1) / 2), 64u}));
+}
+
+// work(w) on up to T threads, the caller's own among them (fewer when the
+// system gives no more); false if one of them ran out of memory.
+template <class F>
+bool on_threads(uint32_t T, F&& work) {
+  std::atomic<bool> ok{true};
+  auto guarded = [&](uint32_t w) {
+    try {
+      work(w);
+    } catch (const std::bad_alloc&) {
+      ok = false;
+    }
+  };
+  std::vector<std::thread> pool;
+  try {
+    pool.reserve(T - 1);
+    for (uint32_t w = 1; w < T; ++w) pool.emplace_back(guarded, w);
+  } catch (const std::system_error&) {
+  } catch (const std::bad_alloc&) {
+  }
+  guarded(0);
+  for (auto& t : pool) t.join();
+  return ok;
+}
+
+// The ranges in the order the threads take them: the longest first, so that
+// none of them starts last.
+std::vector<uint32_t> longest_first(uint32_t n, const uint64_t* lens) {
+  std::vector<uint32_t> order(n);
+  for (uint32_t i = 0; i < n; ++i) order[i] = i;
+  std::stable_sort(order.begin(), order.end(), [&](uint32_t x, uint32_t y) { return lens[x] > lens[y]; });
+  return order;
 }
 
 // Closure of one range: every position whose byte the range's bytes depend
@@ -128,7 +201,9 @@ void closure_of(const aceapex_decoder* d, uint64_t off, uint64_t len, NeedSet& n
         if (dst >= iv.second) break;
         const uint64_t k0 = std::max(iv.first, dst) - dst, k1 = std::min(iv.second, dst + n) - dst;
         const uint64_t dist = dst - src[t];
-        if (k1 - k0 >= dist) {
+        if (k1 <= dist) {  // the first period: no wrap (most matches, and no division)
+          need.insert(src[t] + k0, src[t] + k1, work);
+        } else if (k1 - k0 >= dist) {
           need.insert(src[t], src[t] + std::min(n, dist), work);
         } else {
           const uint64_t a = k0 % dist, b = a + (k1 - k0);
@@ -163,24 +238,23 @@ int union_closure(const aceapex_decoder* d, uint32_t n, const uint64_t* offs, co
   for (uint32_t i = 0; i < n; ++i)
     if (offs[i] > N || lens[i] > N - offs[i]) return ax::fail(AX_E_RANGE, "range outside the archive");
   if (d->idx_dstlen.size() != d->info.n_matches) return ax::fail(AX_E_ARG, "token index not built");
-  const uint32_t T = closure_threads(n, lens, threads);
-  std::vector<std::vector<uint64_t>> part(T);
-  std::atomic<uint32_t> next{0};
-  auto worker = [&](uint32_t w) {
-    for (;;) {
-      const uint32_t i = next.fetch_add(1);
-      if (i >= n) break;
-      if (!lens[i] || cached_closure(d, offs[i], lens[i], part[w])) continue;
-      NeedSet need(d->info.block_size);
-      closure_of(d, offs[i], lens[i], need);
-      need.blocks(part[w]);
-    }
-  };
-  std::vector<std::thread> pool;
   try {
-    for (uint32_t w = 1; w < T; ++w) pool.emplace_back(worker, w);
-    worker(0);
-    for (auto& t : pool) t.join();
+    const uint32_t T = closure_threads(n, lens, threads);
+    std::vector<std::vector<uint64_t>> part(T);
+    const std::vector<uint32_t> order = longest_first(n, lens);
+    std::atomic<uint32_t> next{0};
+    const bool ok = on_threads(T, [&](uint32_t w) {
+      for (;;) {
+        const uint32_t k = next.fetch_add(1);
+        if (k >= n) break;
+        const uint32_t i = order[k];
+        if (!lens[i] || cached_closure(d, offs[i], lens[i], part[w])) continue;
+        NeedSet need(d->info.block_size);
+        closure_of(d, offs[i], lens[i], need);
+        need.blocks(part[w]);
+      }
+    });
+    if (!ok) return ax::fail(AX_E_NOMEM, "closure");
     blocks.clear();
     for (auto& p : part) blocks.insert(blocks.end(), p.begin(), p.end());
     std::sort(blocks.begin(), blocks.end());
@@ -413,41 +487,32 @@ int aceapex_closure_sizes(const aceapex_decoder* d, uint32_t n, const uint64_t* 
   for (uint32_t i = 0; i < n; ++i)
     if (offs[i] > N || lens[i] > N - offs[i]) return ax::fail(AX_E_RANGE, "range outside the archive");
   if (d->idx_dstlen.size() != d->info.n_matches) return ax::fail(AX_E_ARG, "token index not built");
-  const uint32_t T = closure_threads(n, lens, threads);
-  std::atomic<uint32_t> next{0};
-  std::atomic<int> failed{0};
-  auto worker = [&]() {
-    std::vector<uint64_t> bl;
-    for (;;) {
-      const uint32_t i = next.fetch_add(1);
-      if (i >= n) break;
-      bl.clear();
-      if (lens[i] && !cached_closure(d, offs[i], lens[i], bl)) {
-        try {
+  bool ok = false;
+  try {
+    const std::vector<uint32_t> order = longest_first(n, lens);
+    std::atomic<uint32_t> next{0};
+    ok = on_threads(closure_threads(n, lens, threads), [&](uint32_t) {
+      std::vector<uint64_t> bl;
+      for (;;) {
+        const uint32_t k = next.fetch_add(1);
+        if (k >= n) break;
+        const uint32_t i = order[k];
+        bl.clear();
+        if (lens[i] && !cached_closure(d, offs[i], lens[i], bl)) {
           NeedSet need(d->info.block_size);
           closure_of(d, offs[i], lens[i], need);
           need.blocks(bl);
           cache_closure(d, offs[i], lens[i], bl.data(), bl.size());
-        } catch (const std::bad_alloc&) {
-          failed = 1;
-          break;
         }
+        uint64_t t = 0;
+        for (uint64_t b : bl) t += d->mpre[b + 1] - d->mpre[b];
+        blocks[i] = bl.size();
+        tokens[i] = t;
       }
-      uint64_t t = 0;
-      for (uint64_t b : bl) t += d->mpre[b + 1] - d->mpre[b];
-      blocks[i] = bl.size();
-      tokens[i] = t;
-    }
-  };
-  try {
-    std::vector<std::thread> pool;
-    for (uint32_t w = 1; w < T; ++w) pool.emplace_back(worker);
-    worker();
-    for (auto& t : pool) t.join();
-  } catch (const std::system_error&) {
-    return ax::fail(AX_E_NOMEM, "closure threads");
+    });
+  } catch (const std::bad_alloc&) {
   }
-  return failed ? ax::fail(AX_E_NOMEM, "closure") : AX_OK;
+  return ok ? AX_OK : ax::fail(AX_E_NOMEM, "closure");
 }
 
 int aceapex_closure_blocks(aceapex_decoder* d, uint32_t n, const uint64_t* offs, const uint64_t* lens,
