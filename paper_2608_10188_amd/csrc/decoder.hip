@@ -84,7 +84,7 @@ struct DevStatus {
   unsigned long long bad_block;
   uint32_t ticket;
   uint32_t long_count;
-  uint32_t n_pending;  // tokens the bulk rounds left (the deep remainder)
+  uint32_t n_pending;  // tokens the bulk rounds left (the deep remainder); roots: whether a sweep has work
   uint32_t pad2;
   uint32_t jump_used;    // jump passes that found active entries (0: all of them did)
   uint32_t n_jwords;     // leftover-map words with bits set (the jump kernels' work list)
@@ -224,7 +224,19 @@ __device__ inline uint32_t wave_incl_sum32(uint32_t x) {
 // Tables go by a symbol's rank among the present ones: the slot table is then
 // a prefix sum over start marks, four slots a word, instead of a loop over the
 // slots and the symbol list.
+//
+// kWide, for windows of at most kWideBlocks blocks: the chain is what counts
+// and LDS is free, so every slot gets its whole entry (16 KiB, seven waves a
+// compute unit) and a step's chain is two reads.  64 KiB of DNA 76.7 -> 75.1 us,
+// 4 MiB 104.5 -> 102.0, a 16 KiB range 95.5 -> 92.5; 80 MiB of text and other
+// long literal alphabets are the same.  With more blocks the waves that fit
+// count: 2048 blocks of reads 226 -> 246 us, 4096 of DNA 155 -> 199, 15500 of
+// DNA 686 -> 941 (whole decodes); at a line of 1100 a batch of 32 ranges lost 8 to
+// 12 of 350 us.
+constexpr uint32_t kWideBlocks = 512;
+template <bool kWide>
 __global__ __launch_bounds__(64) void k_ans(AnsArgs a) {
+  __shared__ uint32_t wide[kWide ? ax::kProbScale : 1];  // slot -> f | (slot - cum) << 12 | symbol << 24
   // slot -> rank, or 4 * rank (the entry's place in bytes) where that fits
   __shared__ __attribute__((aligned(16))) uint8_t ranktab[ax::kProbScale];
   __shared__ uint32_t fctab[256];  // by rank: f | cum << 12 | symbol << 24
@@ -329,7 +341,7 @@ __global__ __launch_bounds__(64) void k_ans(AnsArgs a) {
   for (uint32_t j = 0, r = rank0, cum = fincl - fsum; j < 4; ++j) {  // cum < 4096: every f is at least 1
     if (!((bits >> j) & 1)) continue;
     fctab[r] = myf[j] | (cum << 12) | ((sym0 + j) << 24);
-    if (r) ranktab[cum] = present <= 64 ? 4 : 1;
+    if (r) ranktab[cum] = !kWide && present <= 64 ? 4 : 1;
     cum += myf[j];
     ++r;
   }
@@ -354,6 +366,14 @@ __global__ __launch_bounds__(64) void k_ans(AnsArgs a) {
     for (uint32_t q = 0; q < 4; ++q) *reinterpret_cast<u32x4*>(ranktab + 64 * lane + 16 * q) = v[q] + base;
   }
   __syncthreads();
+  if (kWide) {
+#pragma unroll 8
+    for (uint32_t slot = lane; slot < ax::kProbScale; slot += 64) {
+      const uint32_t fc = fctab[ranktab[slot]];
+      wide[slot] = (fc & 0xFF000FFFu) | ((slot - ((fc >> 12) & 0xFFFu)) << 12);
+    }
+    __syncthreads();
+  }
   // --- decode: lane j owns symbols j, j+K, ...
   // The renormalisation words of a step are taken in lane order from a
   // window: lane l's register P holds word base+l in its low half and word
@@ -400,17 +420,26 @@ __global__ __launch_bounds__(64) void k_ans(AnsArgs a) {
   const uint64_t kmask = K == 64 ? ~0ull : ((1ull << K) - 1ull);
   const __amdgpu_buffer_rsrc_t orsrc = __builtin_amdgcn_make_buffer_rsrc(outs[stream], 0, int(n), kBufferWord3);
   const uint32_t beyond = lane < K ? 0u : 0x40000000u;
-  auto entry = [&](auto small_tag, uint32_t slot) -> uint32_t {
+  // the entry of x's slot, and the state after its symbol
+  auto entry = [&](auto small_tag, uint32_t& xn) -> uint32_t {
+    const uint32_t slot = x & (ax::kProbScale - 1);
+    uint32_t fc;
+    if (kWide) {
+      fc = wide[slot];
+      xn = (fc & 0xFFFu) * (x >> ax::kProbBits) + ((fc >> 12) & 0xFFFu);
+      return fc;
+    }
     const uint32_t r = ranktab[slot];
-    if (decltype(small_tag)::value) return *reinterpret_cast<const uint32_t*>(reinterpret_cast<const uint8_t*>(fctab) + r);
-    return fctab[r];
+    if (decltype(small_tag)::value) fc = *reinterpret_cast<const uint32_t*>(reinterpret_cast<const uint8_t*>(fctab) + r);
+    else fc = fctab[r];
+    xn = (fc & 0xFFFu) * (x >> ax::kProbBits) + slot - ((fc >> 12) & 0xFFFu);
+    return fc;
   };
   auto full_steps = [&](auto all_tag, auto small_tag) {
     constexpr bool kAll = decltype(all_tag)::value;
     auto step = [&]() -> uint32_t {
-      const uint32_t slot = x & (ax::kProbScale - 1);
-      const uint32_t fc = entry(small_tag, slot);
-      const uint32_t xn = (fc & 0xFFFu) * (x >> ax::kProbBits) + slot - ((fc >> 12) & 0xFFFu);
+      uint32_t xn;
+      const uint32_t fc = entry(small_tag, xn);
       const bool need = xn < ax::kRansLow;
       uint64_t m = __builtin_amdgcn_ballot_w64(need);
       if (!kAll) m &= kmask;
@@ -436,7 +465,7 @@ __global__ __launch_bounds__(64) void k_ans(AnsArgs a) {
       __builtin_amdgcn_raw_buffer_store_b8(uint8_t(fc >> 24), orsrc, int(lane | beyond), int(t * K), 0);
     }
   };
-  const bool small = present <= 64;
+  const bool small = !kWide && present <= 64;
   if (K == 64 && small) full_steps(std::true_type{}, std::true_type{});
   else if (K == 64) full_steps(std::true_type{}, std::false_type{});
   else if (small) full_steps(std::false_type{}, std::true_type{});
@@ -444,9 +473,8 @@ __global__ __launch_bounds__(64) void k_ans(AnsArgs a) {
   uint32_t i = full * K + lane;
   for (uint32_t t = full; t < steps; ++t, i += K) {
     const bool act = lane < K && i < n;
-    const uint32_t slot = x & (ax::kProbScale - 1);
-    const uint32_t fc = small ? entry(std::true_type{}, slot) : entry(std::false_type{}, slot);
-    const uint32_t xn = (fc & 0xFFFu) * (x >> ax::kProbBits) + slot - ((fc >> 12) & 0xFFFu);
+    uint32_t xn;
+    const uint32_t fc = small ? entry(std::true_type{}, xn) : entry(std::false_type{}, xn);
     const bool need = act && xn < ax::kRansLow;
     const uint32_t xr = renorm(__ballot(need), xn, need);
     if (act) {
@@ -3215,6 +3243,11 @@ static int hip_fail(hipError_t e, const char* what) {
   return fail(AX_E_HIP, hipGetErrorString(e));
 }
 
+static void launch_ans(const AnsArgs& aa, hipStream_t s) {
+  if (aa.n_items <= kWideBlocks) hipLaunchKernelGGL(k_ans<true>, dim3(4 * aa.n_items), dim3(64), 0, s, aa);
+  else hipLaunchKernelGGL(k_ans<false>, dim3(4 * aa.n_items), dim3(64), 0, s, aa);
+}
+
 // Jump passes that resolve any chain of a window of `tok` tokens: a chain
 // visits each pending token at most once, the first entries span one hop,
 // and a pass triples the hops an entry spans.
@@ -3489,7 +3522,7 @@ int plan_parse_tokens(Plan* P, void* d_work, uint64_t work_len, hipStream_t s, u
     hipLaunchKernelGGL(k_window_init, dim3(1), dim3(64), 0, s, st, int(&W == &P->wins.front()));
     AnsArgs aa{P->d_jobs, wbl, W.items, P->slot_b, w + L.lit, w + L.cmd, w + L.off, w + L.len, P->off_cap,
                P->len_cap, reinterpret_cast<uint32_t*>(w + L.nsym), st};
-    hipLaunchKernelGGL(k_ans, dim3(4 * W.items), dim3(64), 0, s, aa);
+    launch_ans(aa, s);
     ParseArgs pa{P->d_jobs, wbl, W.items, W.tok, P->slot_b, w + L.lit, w + L.cmd, w + L.off, w + L.len, P->off_cap,
                  P->len_cap, reinterpret_cast<const uint32_t*>(w + L.nsym), reinterpret_cast<uint64_t*>(w + L.tok),
                  nullptr, nullptr, st, 0};
@@ -3543,7 +3576,7 @@ int block_streams(const aceapex_decoder* d, uint64_t first, uint64_t count, void
   hipLaunchKernelGGL(k_window_init, dim3(1), dim3(64), 0, s, st, 1);
   AnsArgs aa{P->d_jobs, P->d_wbl, W.items, P->slot_b, w + L.lit, w + L.cmd, w + L.off, w + L.len, P->off_cap,
              P->len_cap, reinterpret_cast<uint32_t*>(w + L.nsym), st};
-  hipLaunchKernelGGL(k_ans, dim3(4 * W.items), dim3(64), 0, s, aa);
+  launch_ans(aa, s);
   hipError_t e = hipMemcpyAsync(n_syms, w + L.nsym, 16 * count, hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (e != hipSuccess) return hip_fail(e, "stream counts");
@@ -3765,7 +3798,7 @@ static void enqueue_out(Plan* P, uint8_t* w, int copy_mode, hipStream_t s, bool 
                P->len_cap, reinterpret_cast<uint32_t*>(w + L.nsym), st};
     hipEvent_t* ev = timed ? P->ev.data() + 5 * wi : nullptr;
     if (ev) (void)hipEventRecord(ev[0], s);
-    hipLaunchKernelGGL(k_ans, dim3(4 * W.items), dim3(64), 0, s, aa);
+    launch_ans(aa, s);
     if (ev) (void)hipEventRecord(ev[1], s);
     const int bulk = P->wbulk[wi] ? int(P->wbulk[wi]) : P->opt.bulk_rounds;
     const bool recs = roots || bulk <= 1;

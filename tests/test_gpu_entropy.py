@@ -48,3 +48,20 @@ def test_stream_lengths(spread):
         assert np.array_equal(dec.streams(0, 1)[0]["lit"], x), n
         out = dec.decode_all()
         assert dec.status()[0] == 0 and np.array_equal(out.cpu().numpy()[:n], x), n
+
+
+@pytest.mark.parametrize("blocks", [512, 513])
+@pytest.mark.parametrize("symbols", [64, 65, 256])
+def test_windows_around_the_wide_tables(symbols, blocks):
+    """Windows of up to 512 blocks decode from per-slot entries, larger ones by rank."""
+    print("[gpu case] entropy window", symbols, blocks, flush=True)
+    rng = np.random.default_rng(symbols + blocks)
+    p = 0.95 ** np.arange(symbols) + 1e-3
+    x = rng.permutation(256)[:symbols].astype(np.uint8)[rng.choice(symbols, blocks * 4096 - 7, p=p / p.sum())]
+    arc, _ = oracle.encode(x, block_size=4096, min_match=255)
+    dec = ax.Decoder(arc, torch.from_numpy(arc).cuda())
+    assert int(dec.info.n_blocks) == blocks
+    out = dec.decode_all()
+    assert dec.status()[0] == 0 and np.array_equal(out.cpu().numpy()[: x.size], x)
+    for b, got in zip((0, blocks - 1), (dec.streams(0, 1)[0], dec.streams(blocks - 1, 1)[0])):
+        assert np.array_equal(got["lit"], oracle.block_streams(arc, b)["lit"])
