@@ -201,3 +201,25 @@ def test_serving_results_same_alone_and_in_mix(dna_archive):
         assert np.array_equal(a, m), i
         assert np.array_equal(m, x[int(off[i]):int(off[i]) + int(ln[i])]), i
     assert np.all(res["latency_ns"] > 0)
+
+
+@pytest.mark.parametrize("n", [1, 8, 9])
+def test_gather_of_sixteen_byte_pieces(dna_archive, n):
+    """Batches on either side of the descriptors that travel with the launch
+    (8), ranges that end or cross a block anywhere in a piece of sixteen bytes
+    or a chunk of 1 KiB, at every destination alignment; guards stay whole."""
+    x, arc = dna_archive
+    d = _decoder_with_index(arc)
+    rp = ax.RangePlan(d, max_blocks=512, max_tokens=1 << 18)
+    work = torch.empty(rp.workspace_bytes, dtype=torch.uint8, device="cuda")
+    _say("gather", n)
+    rs = [(9 * B - k, k + t) for k in (1, 15, 16, 17, 1008, 1023, 1024) for t in (0, 1, 15, 16, 17, 1025)]
+    for i in range(0, len(rs), n):
+        part = rs[i:i + n]
+        bufs = [torch.full((ln + 32,), 0xCC, dtype=torch.uint8, device="cuda") for _, ln in part]
+        at = [(i + j) % 16 + 1 for j in range(len(part))]
+        rp.decode([o for o, _ in part], [ln for _, ln in part], [b[a: a + r[1]] for b, a, r in zip(bufs, at, part)], work)
+        for b, a, (off, ln) in zip(bufs, at, part):
+            got = b.cpu().numpy()
+            assert np.array_equal(got[a: a + ln], x[off: off + ln]), (off, ln, a)
+            assert (got[:a] == 0xCC).all() and (got[a + ln:] == 0xCC).all(), (off, ln, a)
