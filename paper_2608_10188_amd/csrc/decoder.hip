@@ -66,6 +66,16 @@ typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
 
 constexpr uint32_t kMaxB = 16384;           // largest block the device path decodes
 constexpr uint32_t kParseThreads = 256;
+// Windows of few blocks parse them with more threads, so in fewer chunks: a
+// chunk is a chain of block-wide steps whose latency hardly grows with it.
+// Whole decodes with 256, 512 and 1024 threads, in us: 4 blocks of DNA 75, 65,
+// 62; 192 of text 83, 78, 76; 256 of DNA 102, 89, 86; 384 of text 100, 94, 97;
+// 512 of DNA 116, 106, 110; 768 of DNA 150, 137, 151, of text 140, 136, 148;
+// 1024 of DNA 153, 142, 166 but of text 165, 168, 181, of reads 173, 180, 192 and
+// of 4 KiB blocks 65, 69, 85; 2048 of reads 224, 233, 264; 15500 of DNA 685,
+// 732, 1043.  A compute unit each is the line for 1024, three blocks for 512.
+constexpr uint32_t kParseWide = 1024, kParseMid = 512;
+constexpr uint32_t kParseWideBlocks = 256, kParseMidBlocks = 768;
 constexpr uint32_t kOffStage = 3072;        // offset-stream bytes staged in LDS by k_parse
 constexpr uint32_t kLenStage = 256;         // length-stream bytes staged in LDS by k_parse
 constexpr uint32_t kLenBpt = 1, kOffBpt = 2;  // LEB bytes per thread per pass: length / offset streams
@@ -546,7 +556,19 @@ __device__ inline uint64_t pick4(const uint64_t h[4], uint64_t j) {
   return j == 0 ? h[0] : j == 1 ? h[1] : j == 2 ? h[2] : h[3];
 }
 
+// Of more than 256 chunk positions a byte names only the lane; the tag byte of
+// a position is then its wave (below 16, an input slot keeps 0xFF).
+__device__ inline HMap map_of_wave(HMap m, uint32_t wv) { return HMap{m.v, m.t | (~m.t & (wv * 0x01010101u))}; }
+__device__ inline HMap map_after_waves(HMap g, HMap f) {
+  const uint32_t hi = g.t & 0x80808080u, in = (hi - (hi >> 7)) | hi;  // 0xFF where an input slot
+  const uint32_t sel = (g.v & in) | (0x07060504u & ~in);
+  return HMap{__builtin_amdgcn_perm(g.v, f.v, sel), __builtin_amdgcn_perm(g.t, f.t, sel)};
+}
+
+template <uint32_t kT>
 struct ParseShared {
+  static constexpr uint32_t kWaves = kT / 64;
+  static_assert(kWaves == 4 || kWaves == 8 || kWaves == 16, "a row of 16 lanes scans the waves");
   // the literal bytes of the 16-byte group a chunk leaves open, by chunk
   // parity (a chunk reads its predecessor's while it may write its own)
   u32x4 gcarry[2];
@@ -554,9 +576,9 @@ struct ParseShared {
   uint64_t startw[kMaxB / 64];    // token starts among them (kRecs)
   uint64_t runbits[kMaxB / 64];   // starts of the chunk's literal runs, in the block's output positions
   uint16_t runpre[kMaxB / 64];    // run starts in earlier words
-  uint16_t rundelta[kParseThreads];  // per run: output position - literal index
-  uint16_t runbeg[kParseThreads];    // per run: first output position
-  uint16_t runend[kParseThreads];    // per run: one past its last output position
+  uint16_t rundelta[kT];  // per run: output position - literal index
+  uint16_t runbeg[kT];    // per run: first output position
+  uint16_t runend[kT];    // per run: one past its last output position
   u32x4 below[17];                // below[k]: sixteen bytes, the first k of them 0xFF
   // the block's decoded offset and length streams, when they fit, and where
   // each of their values ends (one past its last byte)
@@ -564,39 +586,62 @@ struct ParseShared {
   __attribute__((aligned(16))) uint8_t lenb[kLenStage + 16];
   uint16_t offend[kOffStage];
   uint16_t lenend[kLenStage];
-  uint64_t offval[kParseThreads];
-  uint64_t wsum[4][2];
-  HMap wmap[4];
-  uint64_t cdist[kParseThreads];  // distance of the explicit match at each chunk position
+  uint64_t offval[kT];
+  uint64_t wsum[kWaves][2];
+  HMap wmap[kWaves];
+  uint64_t cdist[kT];  // distance of the explicit match at each chunk position
   uint64_t last4[4];              // the chunk's last explicit-match distances, newest first
-  uint32_t wterm[4];
-  int32_t wlast[4];
+  uint32_t wterm[kWaves];
+  int32_t wlast[kWaves];
   uint32_t leb_found, leb_cursor;
   // coverage bits of the 16-byte group a chunk leaves open, by chunk parity
   // (a chunk reads its predecessor's while it may write its own)
   uint32_t mcarry[2];
   int bad;
-  alignas(4) uint8_t anyb[2][4];  // block_any: one byte per wave, two call sites
+  alignas(4) uint8_t anyb[2][kWaves];  // block_any: one byte per wave, two call sites
 };
 
-// Block-wide "any thread's p" (256 threads): a ballot per wave, one LDS byte
+// Block-wide "any thread's p": a ballot per wave, one LDS byte
 // per wave, one barrier.  Slot k's bytes are rewritten only after a later
 // barrier, so every thread has read them.
-__device__ inline bool block_any(bool p, ParseShared& sh, int k) {
+template <class S>
+__device__ inline bool block_any(bool p, S& sh, int k) {
   const bool w = __ballot(p) != 0;
   if (lane_id() == 0) sh.anyb[k][threadIdx.x >> 6] = uint8_t(w);
   __syncthreads();
-  return *reinterpret_cast<const uint32_t*>(sh.anyb[k]) != 0;
+  uint32_t any = 0;
+#pragma unroll
+  for (uint32_t q = 0; q < S::kWaves / 4; ++q) any |= reinterpret_cast<const uint32_t*>(sh.anyb[k])[q];
+  return any != 0;
 }
 
 // Block-wide exclusive scan of a u64 holding two u32 sums (the halves are
-// scanned separately: no half may carry), 256 threads.  One barrier: a slot is
-// written again only after a later one.
-__device__ inline uint64_t block_excl_sum64(uint64_t v, uint64_t* total, ParseShared& sh, int slotk) {
+// scanned separately: no half may carry).  One barrier: a slot is written again
+// only after a later one.  Of more than four waves, each wave scans the sums in
+// its first row of lanes.
+__device__ inline uint32_t row_incl_sum32(uint32_t x) {
+  x += dpp_move<kDppRowShr + 1, 0xF>(0, x);
+  x += dpp_move<kDppRowShr + 2, 0xF>(0, x);
+  x += dpp_move<kDppRowShr + 4, 0xF>(0, x);
+  x += dpp_move<kDppRowShr + 8, 0xF>(0, x);
+  return x;
+}
+template <class S>
+__device__ inline uint64_t block_excl_sum64(uint64_t v, uint64_t* total, S& sh, int slotk) {
   const uint32_t lane = lane_id(), wv = threadIdx.x >> 6;
   const uint64_t x = wave_incl_sum32(uint32_t(v)) | (uint64_t(wave_incl_sum32(uint32_t(v >> 32))) << 32);
   if (lane == 63) sh.wsum[wv][slotk] = x;
   __syncthreads();
+  if constexpr (S::kWaves > 4) {
+    const uint64_t w = lane < S::kWaves ? sh.wsum[lane][slotk] : 0;
+    const uint32_t lo = row_incl_sum32(uint32_t(w)), hi = row_incl_sum32(uint32_t(w >> 32));
+    auto upto = [&](uint32_t k) {  // the sum of waves 0 to k
+      return uint64_t(uint32_t(__builtin_amdgcn_readlane(lo, k))) | (uint64_t(uint32_t(__builtin_amdgcn_readlane(hi, k))) << 32);
+    };
+    *total = upto(S::kWaves - 1);
+    const uint32_t u = __builtin_amdgcn_readfirstlane(wv);
+    return (u ? upto(u - 1) : 0) + x - v;
+  }
   uint64_t pre = 0, tot = 0;
   for (uint32_t k = 0; k < 4; ++k) {
     const uint64_t t = sh.wsum[k][slotk];
@@ -613,7 +658,8 @@ template <int CTRL, int ROWS>
 __device__ inline HMap map_dpp(HMap m) {
   return HMap{dpp_move<CTRL, ROWS>(kMapId.v, m.v), dpp_move<CTRL, ROWS>(kMapId.t, m.t)};
 }
-__device__ inline HMap block_excl_map(HMap m, HMap* total, ParseShared& sh) {
+template <class S>
+__device__ inline HMap block_excl_map(HMap m, HMap* total, S& sh) {
   const uint32_t lane = lane_id(), wv = threadIdx.x >> 6;
   HMap x = m;  // inclusive wave scan, earlier lanes' maps applied first (the identity fills gaps)
   x = map_after(x, map_dpp<kDppRowShr + 1, 0xF>(x));
@@ -622,9 +668,24 @@ __device__ inline HMap block_excl_map(HMap m, HMap* total, ParseShared& sh) {
   x = map_after(x, map_dpp<kDppRowShr + 8, 0xF>(x));
   x = map_after(x, map_dpp<kDppRowBcast15, 0xA>(x));
   x = map_after(x, map_dpp<kDppRowBcast31, 0xC>(x));
+  if constexpr (S::kWaves > 4) x = map_of_wave(x, wv);
   if (lane == 63) sh.wmap[wv] = x;
   __syncthreads();
   HMap pre = kMapId, tot = kMapId;
+  if constexpr (S::kWaves > 4) {
+    HMap w = lane < S::kWaves ? sh.wmap[lane] : kMapId;
+    w = map_after_waves(w, map_dpp<kDppRowShr + 1, 0xF>(w));
+    w = map_after_waves(w, map_dpp<kDppRowShr + 2, 0xF>(w));
+    w = map_after_waves(w, map_dpp<kDppRowShr + 4, 0xF>(w));
+    w = map_after_waves(w, map_dpp<kDppRowShr + 8, 0xF>(w));
+    auto upto = [&](uint32_t k) {
+      return HMap{uint32_t(__builtin_amdgcn_readlane(w.v, k)), uint32_t(__builtin_amdgcn_readlane(w.t, k))};
+    };
+    *total = upto(S::kWaves - 1);
+    const uint32_t u = __builtin_amdgcn_readfirstlane(wv);
+    if (u) pre = upto(u - 1);
+    return map_after_waves(map_dpp<kDppWaveShr1, 0xF>(x), pre);
+  }
   for (uint32_t k = 0; k < 4; ++k) {
     if (k < wv) pre = map_after(sh.wmap[k], pre);
     tot = map_after(sh.wmap[k], tot);
@@ -635,20 +696,23 @@ __device__ inline HMap block_excl_map(HMap m, HMap* total, ParseShared& sh) {
 
 // Distance named by slot k of a map: an input slot of hist, or an explicit
 // match of the chunk.
-__device__ inline uint64_t map_value(HMap m, uint32_t k, const uint64_t hist[4], const ParseShared& sh) {
+template <class S>
+__device__ inline uint64_t map_value(HMap m, uint32_t k, const uint64_t hist[4], const S& sh) {
   const uint32_t g = (m.v >> (8 * k)) & 0xFFu;
+  if constexpr (S::kWaves > 4) {
+    const uint32_t w = (m.t >> (8 * k)) & 0xFFu;
+    return (w >> 7) ? pick4(hist, g & 3) : sh.cdist[64 * w + g];
+  }
   return ((m.t >> (8 * k)) & 1u) ? pick4(hist, g & 3) : sh.cdist[g];
 }
 
 // Decode `count` consecutive LEB128 values starting at byte *cursor of
-// src[0..n) into dst (u64) — all 256 threads, BPT bytes each per window of
-// 256 * BPT.  A byte below 0x80 ends a value; terminators are counted by a block
+// src[0..n) into dst (u64) — all threads, BPT bytes each per window.  A byte below 0x80 ends a value; terminators are counted by a block
 // scan, and each terminator's thread assembles its value from the bytes after
 // the previous terminator.  Returns false on a malformed or missing value.
 // *cursor advances past the last value.
-template <uint32_t BPT, class Src>
-__device__ bool leb_values(Src src, uint32_t n, uint32_t* cursor, uint32_t count, uint64_t* dst,
-                           ParseShared& sh) {
+template <uint32_t BPT, class Src, class S>
+__device__ bool leb_values(Src src, uint32_t n, uint32_t* cursor, uint32_t count, uint64_t* dst, S& sh) {
   const uint32_t t = threadIdx.x, lane = lane_id(), wv = t >> 6;
   const uint32_t first = *cursor;
   uint32_t found = 0;
@@ -672,7 +736,7 @@ __device__ bool leb_values(Src src, uint32_t n, uint32_t* cursor, uint32_t count
     if (hm == 0 ? lane == 0 : lane == uint32_t(63 - __clzll(hm))) sh.wlast[wv] = mylast;
     __syncthreads();
     uint32_t before = incl - c, all = 0;
-    for (uint32_t k = 0; k < 4; ++k) {
+    for (uint32_t k = 0; k < S::kWaves; ++k) {
       if (k < wv) before += sh.wterm[k];
       all += sh.wterm[k];
     }
@@ -704,12 +768,12 @@ __device__ bool leb_values(Src src, uint32_t n, uint32_t* cursor, uint32_t count
     }
     // the value still open at the end of this window starts after its last terminator
     int32_t last = -1;
-    for (int32_t k = 3; k >= 0; --k)
+    for (int32_t k = int32_t(S::kWaves) - 1; k >= 0; --k)
       if (sh.wlast[k] >= 0) { last = sh.wlast[k]; break; }
     if (last >= 0) value_start = uint32_t(last) + 1;
-    if (win + BPT * kParseThreads - value_start > 10 && found + all < count) ok = false;  // a value longer than 10 bytes
+    if (win + BPT * 64 * S::kWaves - value_start > 10 && found + all < count) ok = false;  // a value longer than 10 bytes
     found += all;
-    win += BPT * kParseThreads;
+    win += BPT * 64 * S::kWaves;
     __syncthreads();
   }
   if (block_any(!ok, sh, 0)) return false;
@@ -747,31 +811,30 @@ __device__ inline bool leb_staged(const uint8_t* src, const uint16_t* end, uint3
   return n == 10 && (hi & 0xFF00u) <= 0x100u;
 }
 
-// Seven waves per SIMD (at most 72 VGPRs), as many as the LDS allows (six: 254 MB
-// DNA 741 instead of 728 us, eight: 768).
+// Of 256 threads seven waves per SIMD (at most 72 VGPRs), as many as the LDS
+// allows (six: 254 MB DNA 741 instead of 728 us, eight: 768).
 //
-// A chunk of 256 commands is a chain of block-wide steps: with few blocks in
+// A chunk, a command per thread, is a chain of block-wide steps: with few blocks in
 // flight its latency counts, with many the instructions issued.  The values
 // of the offset and length streams are therefore found once per block (one
 // scan over the staged bytes lists where every value ends) and read by the
 // command that needs them, instead of a scan over a window of the stream for
 // every chunk: 64 KiB of DNA parse in 42 -> 29 us, 254 MB in 253 -> 208 us.
-template <class O, bool kRecs>
-__global__ __launch_bounds__(kParseThreads, 7) void k_parse(ParseArgs a) {
-  __shared__ ParseShared sh;
+template <class O, bool kRecs, uint32_t kT>
+__global__ __launch_bounds__(kT, kT == kParseThreads ? 7 : 4) void k_parse(ParseArgs a) {
+  __shared__ ParseShared<kT> sh;
   const uint32_t item = blockIdx.x, t = threadIdx.x;
   const uint8_t* cmd = a.cmd + uint64_t(item) * a.slot_b;
   const AX_GLOBAL uint8_t* const litg = gp(a.lit + uint64_t(item) * a.slot_b);
   const uint8_t* offs = a.off + uint64_t(item) * a.off_cap;
   const uint8_t* lens = a.len + uint64_t(item) * a.len_cap;
   // loads that need only the block's place in the window come first: the
-  // chunk's command bytes (inside the slot whatever the count: kParseThreads
-  // <= slot_b) and one 16-byte piece per thread of the offset and length
+  // chunk's command bytes (inside the slot whatever the count) and one 16-byte piece per thread of the offset and length
   // streams, staged in LDS if the stream fits the stage (the slots are
   // 16-aligned and their capacities multiples of 16, so the loads stay in this
   // block's slots)
-  static_assert(kOffStage <= 16 * kParseThreads && kLenStage <= 16 * kParseThreads, "one piece per thread");
-  uint32_t cnext = gp(cmd)[t];
+  static_assert(kOffStage <= 16 * kT && kLenStage <= 16 * kT, "one piece per thread");
+  uint32_t cnext = t < a.slot_b ? gp(cmd)[t] : 0u;
   u32x4 po = {0, 0, 0, 0}, pl = {0, 0, 0, 0};
   if (16 * t < min(kOffStage, a.off_cap)) po = *reinterpret_cast<const AX_GLOBAL u32x4*>(gp(offs) + 16 * t);
   if (16 * t < min(kLenStage, a.len_cap)) pl = *reinterpret_cast<const AX_GLOBAL u32x4*>(gp(lens) + 16 * t);
@@ -791,7 +854,7 @@ __global__ __launch_bounds__(kParseThreads, 7) void k_parse(ParseArgs a) {
   if (t == 0)
     sh.bad = (n_lit > B || n_cmd > B || n_len > job_len_cap(J) || n_off > job_off_cap(J)) ? 1 : 0;
   if (kRecs && t < kMaxB / 64) sh.covw[t] = 0, sh.startw[t] = 0;
-  static_assert(kMaxB / 64 <= kParseThreads, "one map word per thread");
+  static_assert(kMaxB / 64 <= kT, "one map word per thread");
   // the block's output bytes (contiguous); groups below `full` are whole
   AX_GLOBAL uint8_t* const o = a.write_out ? O(J).at(bs) : nullptr;
   const uint32_t full = blen & ~15u;
@@ -825,11 +888,11 @@ __global__ __launch_bounds__(kParseThreads, 7) void k_parse(ParseArgs a) {
   uint32_t dst = 0, litp = 0, offc = 0, lenc = 0;  // offc, lenc: staged, values taken; else bytes
   uint64_t ntok = 0;
   uint64_t hist[4] = {1, 2, 3, 4};
-  for (uint32_t c0 = 0; c0 < n_cmd && !failed; c0 += kParseThreads) {
+  for (uint32_t c0 = 0; c0 < n_cmd && !failed; c0 += kT) {
     const uint32_t i = c0 + t;
     const bool valid = i < n_cmd;
     const uint32_t c = valid ? cnext : 0u;
-    cnext = i + kParseThreads < n_cmd ? cmd[i + kParseThreads] : 0u;  // the next chunk's, in flight meanwhile
+    cnext = i + kT < n_cmd ? cmd[i + kT] : 0u;  // the next chunk's, in flight meanwhile
     const uint32_t kind = c & 3;
     bool bad = valid && kind == 3;
     const uint32_t v = kind == 2 ? (c >> 4) : (c >> 2);
@@ -895,7 +958,7 @@ __global__ __launch_bounds__(kParseThreads, 7) void k_parse(ParseArgs a) {
     if (n_rep) {  // repeat matches read the history: scan the command maps
       HMap mine = kMapId;
       if (is1) {
-        mine = HMap{t | 0x02010000u, 0xFFFFFF00u};
+        mine = HMap{(kT == 256 ? t : t & 63u) | 0x02010000u, 0xFFFFFF00u};
       } else if (is2) {
         const uint32_t r = (c >> 2) & 3;
         mine = HMap{r | ((r >= 1 ? 0u : 1u) << 8) | ((r >= 2 ? 1u : 2u) << 16) | ((r >= 3 ? 2u : 3u) << 24),
@@ -952,7 +1015,7 @@ __global__ __launch_bounds__(kParseThreads, 7) void k_parse(ParseArgs a) {
     // 16-byte store (zeros where matches will be).  The group the chunk ends
     // in is carried to the next chunk, which begins in it
     const uint32_t dend = dst + uint32_t(ptot & 0xFFFFFFFFu);
-    for (uint32_t c = (dst >> 4) + t; 16 * c < dend; c += kParseThreads) {
+    for (uint32_t c = (dst >> 4) + t; 16 * c < dend; c += kT) {
       const uint32_t d0 = max(16 * c, dst), d1 = min(16 * c + 16, dend), w = d0 >> 6;
       int32_t r = int32_t(sh.runpre[w] + __popcll(sh.runbits[w] & (~0ull >> (63 - (d0 & 63))))) - 1;
       if (r < 0 || d0 >= sh.runend[r]) ++r;  // the run holding d0, else the next one
@@ -970,7 +1033,7 @@ __global__ __launch_bounds__(kParseThreads, 7) void k_parse(ParseArgs a) {
         lit16 |= m16;
         if (sh.runend[r] >= d1) break;
       }
-      const uint32_t par = (c0 / kParseThreads) & 1;
+      const uint32_t par = (c0 / kT) & 1;
       const bool head = d0 > 16 * c, open = d1 < 16 * c + 16 && d1 < blen;  // begun in / goes on in another chunk
       if (kRecs) {  // match coverage of the group: its bytes in this chunk that no literal fills
         uint32_t m = ((1u << (d1 - 16 * c)) - 1u) & ~((1u << (d0 - 16 * c)) - 1u) & ~lit16;
@@ -1007,7 +1070,7 @@ __global__ __launch_bounds__(kParseThreads, 7) void k_parse(ParseArgs a) {
   }
   if (!kRecs) return;
   // the records the match layer looks sources up in: two per thread
-  const uint64_t cw = sh.covw[t], sw = sh.startw[t];
+  const uint64_t cw = t < kMaxB / 64 ? sh.covw[t] : 0, sw = t < kMaxB / 64 ? sh.startw[t] : 0;
   uint64_t all;
   const uint32_t pre = uint32_t(tok_lo) + uint32_t(block_excl_sum64(uint64_t(__popcll(sw)), &all, sh, 0));
   if (t < B / 64) {
@@ -3530,7 +3593,7 @@ int plan_parse_tokens(Plan* P, void* d_work, uint64_t work_len, hipStream_t s, u
     ParseArgs pa{P->d_jobs, wbl, W.items, W.tok, P->slot_b, w + L.lit, w + L.cmd, w + L.off, w + L.len, P->off_cap,
                  P->len_cap, reinterpret_cast<const uint32_t*>(w + L.nsym), reinterpret_cast<uint64_t*>(w + L.tok),
                  nullptr, nullptr, st, 0};
-    hipLaunchKernelGGL((k_parse<OutDirect, false>), dim3(W.items), dim3(kParseThreads), 0, s, pa);
+    hipLaunchKernelGGL((k_parse<OutDirect, false, kParseThreads>), dim3(W.items), dim3(kParseThreads), 0, s, pa);
     try {
       tk.resize(2ull * W.tok);
     } catch (const std::bad_alloc&) {
@@ -3809,8 +3872,14 @@ static void enqueue_out(Plan* P, uint8_t* w, int copy_mode, hipStream_t s, bool 
     ParseArgs pa{P->d_jobs, wbl, W.items, W.tok, P->slot_b, w + L.lit, w + L.cmd, w + L.off, w + L.len, P->off_cap,
                  P->len_cap, reinterpret_cast<const uint32_t*>(w + L.nsym), reinterpret_cast<uint64_t*>(w + L.tok),
                  roots ? nullptr : reinterpret_cast<uint32_t*>(w + L.tblk), w + L.done, st, 1};
-    if (recs) hipLaunchKernelGGL((k_parse<O, true>), dim3(W.items), dim3(kParseThreads), 0, s, pa);
-    else hipLaunchKernelGGL((k_parse<O, false>), dim3(W.items), dim3(kParseThreads), 0, s, pa);
+    if (!recs)
+      hipLaunchKernelGGL((k_parse<O, false, kParseThreads>), dim3(W.items), dim3(kParseThreads), 0, s, pa);
+    else if (W.items <= kParseWideBlocks)
+      hipLaunchKernelGGL((k_parse<O, true, kParseWide>), dim3(W.items), dim3(kParseWide), 0, s, pa);
+    else if (W.items <= kParseMidBlocks)
+      hipLaunchKernelGGL((k_parse<O, true, kParseMid>), dim3(W.items), dim3(kParseMid), 0, s, pa);
+    else
+      hipLaunchKernelGGL((k_parse<O, true, kParseThreads>), dim3(W.items), dim3(kParseThreads), 0, s, pa);
     if (ev) (void)hipEventRecord(ev[2], s);
     if (roots) {
       if (ntok) enqueue_roots<O>(P, W, wbl, w, s, ev);
