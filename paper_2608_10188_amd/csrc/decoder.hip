@@ -3335,9 +3335,13 @@ static uint32_t jump_pass_bound(uint64_t tok) {
 // at 16 MiB the walks win again (172 against 191 us).
 constexpr uint64_t kDeepRatio = 3;
 constexpr uint64_t kDeepSmall = 8u << 20;  // positions of a small plan
-// So many deep blocks are finished run by run (eight launches, each reading
-// settled bytes); fewer in one launch that follows the entries.
-constexpr uint32_t kPartBlocks = 2048;
+// Deep blocks of so many positions are finished run by run (eight launches, each
+// reading settled bytes); fewer in one launch that follows the entries.  Whole
+// decodes of text in eight launches and in one: 8 MiB 127 and 110 us, 16 MiB 167
+// and 168, 24 MiB 207 and 227, 32 MiB 250 and 288, with 4, 8 or 16 KiB blocks.
+// Chains end in their own archive, so those of a batch cross fewer runs: 40
+// archives of up to 4 MiB, 16.4 MiB of them deep, 481 and 447.
+constexpr uint64_t kPartPositions = 16u << 20, kPartPositionsBatch = 32u << 20;
 
 // Host tables of a plan: jobs, window blocks, windows, maxima.
 static int build_tables(Plan* P, const std::vector<JobSpec>& specs) {
@@ -3821,7 +3825,8 @@ static void enqueue_roots(Plan* P, const Plan::Win& W, const WinBlock* wbl, uint
     sa.b0 = b0, sa.b1 = b1, sa.settled = 0;
     if (all) hipLaunchKernelGGL(k_sweep<true>, sgrid, dim3(kCopyThreads), 0, s, sa);
     else hipLaunchKernelGGL(k_sweep<false>, sgrid, dim3(kCopyThreads), 0, s, sa);
-    const uint32_t parts = all && b1 - b0 >= kPartBlocks ? kXcds : 1;
+    const uint64_t line = P->jobs.size() == 1 ? kPartPositions : kPartPositionsBatch;
+    const uint32_t parts = all && uint64_t(b1 - b0) << s_log2 >= line ? kXcds : 1;
     for (uint32_t k = 0; k < parts; ++k) {
       sa.b0 = b0 + uint32_t(uint64_t(b1 - b0) * k / parts), sa.b1 = b0 + uint32_t(uint64_t(b1 - b0) * (k + 1) / parts);
       sa.settled = parts > 1;

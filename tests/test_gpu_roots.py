@@ -148,3 +148,14 @@ def test_offset_streams_around_the_stage(n_off, wide):
     dec.build_index()
     src, dst, ln = dec.tokens(0, len(rows) - 2)
     assert [(int(a), int(b), int(c)) for a, b, c in zip(src, dst, ln)] == [(r[3], r[1], r[2]) for r in rows[1:-1]]
+
+
+@pytest.mark.parametrize("blocks", [4095, 4096, 5001])
+def test_finish_in_one_launch_and_in_eight(blocks):
+    """Deep archives around the 16 MiB of positions that are finished run by run."""
+    x, arc = _archive(blocks * 4096 - 9, 4096, blocks, ONE, 12)
+    dec = ax.Decoder(arc, torch.from_numpy(arc).cuda())
+    assert dec.info.payload_bytes < x.size // 3
+    _say("finish", blocks)
+    out = dec.decode_all()
+    assert dec.status()[0] == 0 and np.array_equal(out.cpu().numpy()[: x.size], x)
