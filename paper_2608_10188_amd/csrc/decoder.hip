@@ -2640,11 +2640,11 @@ __device__ inline void tile_or(uint32_t* tile, uint32_t at, B16 v) {
 // a 16-byte chunk of the block is finished by OR-ing the tile into it, and
 // chunks without match bytes are not touched.
 template <class O>
-__global__ __launch_bounds__(kCopyThreads, 8) void k_roots(RootArgs a) {
+__device__ __forceinline__ void roots_block(const RootArgs& a, uint32_t block, uint32_t blocks) {
   __shared__ __attribute__((aligned(16))) uint32_t tile[kMaxB / 4 + 4];  // the last item's fifth word
   __shared__ uint64_t row[kMaxB / 64];                                   // the block's pending bytes
   __shared__ uint32_t heads[kCopyThreads];                               // per wave: tokens starting at an item
-  const uint32_t lane = lane_id(), item = a.first + xcd_item(blockIdx.x, gridDim.x);
+  const uint32_t lane = lane_id(), item = a.first + xcd_item(block, blocks);
   const WinBlock wb = a.wbl[item];
   const uint32_t t1 = item + 1 < a.n_items ? a.wbl[item + 1].tok : a.n_tok;
   const AX_GLOBAL u64x2* const tok = reinterpret_cast<const AX_GLOBAL u64x2*>(gp(a.tok));
@@ -2784,8 +2784,8 @@ constexpr uint32_t kMarkSmallLog2 = 10, kMarkLog2 = 12;
 // its source, any other holds its value.  The bitmap has every byte of the
 // block.
 template <class O>
-__global__ __launch_bounds__(kCopyThreads) void k_mark(RootArgs a) {
-  const uint32_t part = xcd_item(blockIdx.x, gridDim.x), lp = a.s_log2 - a.mark_log2;  // parts per block: 2^lp
+__device__ __forceinline__ void mark_part(const RootArgs& a, uint32_t block, uint32_t blocks) {
+  const uint32_t part = xcd_item(block, blocks), lp = a.s_log2 - a.mark_log2;  // parts per block: 2^lp
   const uint32_t item = part >> lp, p0 = (part & ((1u << lp) - 1u)) << a.mark_log2;
   const WinBlock wb = a.wbl[item];
   const JobDev& J = a.jobs[wb.job];
@@ -2844,6 +2844,26 @@ __global__ __launch_bounds__(kCopyThreads) void k_mark(RootArgs a) {
     gp(a.lmap)[uint64_t(item) * sw + (w >> 6)] = w + 64 <= blen ? ~0ull : w < blen ? (1ull << (blen - w)) - 1 : 0ull;
   }
   if (part == 0 && threadIdx.x == 0) a.st->n_pending = 1;
+}
+
+template <class O>
+__global__ __launch_bounds__(kCopyThreads, 8) void k_roots(RootArgs a) {
+  roots_block<O>(a, blockIdx.x, gridDim.x);
+}
+template <class O>
+__global__ __launch_bounds__(kCopyThreads) void k_mark(RootArgs a) {
+  mark_part<O>(a, blockIdx.x, gridDim.x);
+}
+// A window of deep and other archives takes both at once (the first n_roots
+// workgroups walk), and so its sweeps and finishes: neither kind waits for the
+// other's last workgroups.  40 archives of 61 MiB in all, 16.4 of them deep, 443
+// us with a launch per kind, 407 with one for both (marking still by itself 419;
+// half the sweep's workgroups for each kind 432, the deep ones first 412).  Seven
+// waves a SIMD: the two bodies in one kernel spill with eight.
+template <class O>
+__global__ __launch_bounds__(kCopyThreads, 7) void k_settle(RootArgs a, uint32_t n_roots) {
+  if (blockIdx.x < n_roots) roots_block<O>(a, blockIdx.x, n_roots);
+  else mark_part<O>(a, blockIdx.x - n_roots, gridDim.x - n_roots);
 }
 
 // ---- pending bytes: sweep and finish
@@ -2923,11 +2943,10 @@ __device__ inline uint32_t queue_words(const uint64_t* lmap, uint64_t w0, uint64
 
 // kAll: every byte of the blocks has an entry (k_mark), so a hop is one load.
 template <bool kAll>
-__global__ __launch_bounds__(kCopyThreads) void k_sweep(SweepArgs a) {
-  __shared__ WordQueue queues[kCopyThreads / 64];
+__device__ __forceinline__ void sweep_run(const SweepArgs& a, uint32_t block, uint32_t blocks, WordQueue* queues) {
   if (a.st->n_pending == 0 || __hip_atomic_load(&a.st->err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) return;
-  const uint32_t lane = lane_id(), g = blockIdx.x / kXcds;
-  const uint32_t run = blockIdx.x % kXcds, runs = kXcds;
+  const uint32_t lane = lane_id(), g = block / kXcds;
+  const uint32_t run = block % kXcds, runs = kXcds;
   const uint64_t nb = a.b1 - a.b0;
   const uint32_t b0 = a.b0 + uint32_t(nb * run / runs), b1 = a.b0 + uint32_t(nb * (run + 1) / runs);
   const uint32_t lo = b0 << a.s_log2, wl = a.s_log2 - 6;
@@ -2936,7 +2955,7 @@ __global__ __launch_bounds__(kCopyThreads) void k_sweep(SweepArgs a) {
   WordQueue& q = queues[threadIdx.x >> 6];
   const PosOut po(a);
   const uint64_t wave = uint64_t(g) * (kCopyThreads / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const uint64_t waves = uint64_t(gridDim.x / kXcds) * (kCopyThreads / 64);
+  const uint64_t waves = uint64_t(blocks / kXcds) * (kCopyThreads / 64);
   const uint64_t n = uint64_t(b1 - b0) << wl;
   for (uint64_t i = 0; i * 64 * waves < n; ++i) {
     const uint32_t cnt = queue_words<kAll ? kAllChunk : kFewChunk>(a.lmap, uint64_t(b0) << wl, n, wave, waves, i, q);
@@ -3007,16 +3026,15 @@ __global__ __launch_bounds__(kCopyThreads) void k_sweep(SweepArgs a) {
 // settled (launches in order) such a byte is read from the output; else the
 // entries are followed to the value, over at most one entry per run.
 template <bool kAll>
-__global__ __launch_bounds__(kCopyThreads) void k_finish(SweepArgs a) {
-  __shared__ WordQueue queues[kCopyThreads / 64];
+__device__ __forceinline__ void finish_part(const SweepArgs& a, uint32_t block, uint32_t blocks, WordQueue* queues) {
   if (a.st->n_pending == 0 || __hip_atomic_load(&a.st->err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) return;
   const uint32_t lane = lane_id(), wl = a.s_log2 - 6, lo = a.settled ? a.b0 << a.s_log2 : 0u;
   const AX_GLOBAL uint32_t* const J = gp(a.J);
   const AX_GLOBAL uint64_t* const lm = gp(a.lmap);
   WordQueue& q = queues[threadIdx.x >> 6];
   const PosOut po(a);
-  const uint64_t wave = uint64_t(blockIdx.x) * (kCopyThreads / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const uint64_t waves = uint64_t(gridDim.x) * (kCopyThreads / 64);
+  const uint64_t wave = uint64_t(block) * (kCopyThreads / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint64_t waves = uint64_t(blocks) * (kCopyThreads / 64);
   const uint64_t n = uint64_t(a.b1 - a.b0) << wl;
   const uint32_t sub = lane >> 4, q4 = 4 * (lane & 15u);
   for (uint64_t i = 0; i * 64 * waves < n; ++i) {
@@ -3098,6 +3116,28 @@ __global__ __launch_bounds__(kCopyThreads) void k_finish(SweepArgs a) {
       }
     }
   }
+}
+
+template <bool kAll>
+__global__ __launch_bounds__(kCopyThreads) void k_sweep(SweepArgs a) {
+  __shared__ WordQueue queues[kCopyThreads / 64];
+  sweep_run<kAll>(a, blockIdx.x, gridDim.x, queues);
+}
+template <bool kAll>
+__global__ __launch_bounds__(kCopyThreads) void k_finish(SweepArgs a) {
+  __shared__ WordQueue queues[kCopyThreads / 64];
+  finish_part<kAll>(a, blockIdx.x, gridDim.x, queues);
+}
+// both kinds: the first n_few workgroups (a multiple of kXcds) take `few`
+__global__ __launch_bounds__(kCopyThreads) void k_sweep_both(SweepArgs few, SweepArgs all, uint32_t n_few) {
+  __shared__ WordQueue queues[kCopyThreads / 64];
+  if (blockIdx.x < n_few) sweep_run<false>(few, blockIdx.x, n_few, queues);
+  else sweep_run<true>(all, blockIdx.x - n_few, gridDim.x - n_few, queues);
+}
+__global__ __launch_bounds__(kCopyThreads) void k_finish_both(SweepArgs few, SweepArgs all, uint32_t n_few) {
+  __shared__ WordQueue queues[kCopyThreads / 64];
+  if (blockIdx.x < n_few) finish_part<false>(few, blockIdx.x, n_few, queues);
+  else finish_part<true>(all, blockIdx.x - n_few, gridDim.x - n_few, queues);
 }
 
 // A range decode's slot table: the window's blocks (one window) take slots
@@ -3811,31 +3851,44 @@ static void enqueue_roots(Plan* P, const Plan::Win& W, const WinBlock* wbl, uint
                     J, lmap, st, W.deep,
                     uint64_t(W.deep) << s_log2 <= kDeepSmall ? kMarkSmallLog2 : kMarkLog2};
   const uint32_t shallow = W.items - W.deep;
-  if (W.deep) hipLaunchKernelGGL(k_mark<O>, dim3(W.deep << (s_log2 - ra.mark_log2)), dim3(kCopyThreads), 0, s, ra);
-  if (shallow) hipLaunchKernelGGL(k_roots<O>, dim3(shallow), dim3(kCopyThreads), 0, s, ra);
+  const uint32_t marks = W.deep << (s_log2 - ra.mark_log2);
+  const bool both = W.deep && shallow;
+  if (both) hipLaunchKernelGGL(k_settle<O>, dim3(shallow + marks), dim3(kCopyThreads), 0, s, ra, shallow);
+  else if (W.deep) hipLaunchKernelGGL(k_mark<O>, dim3(marks), dim3(kCopyThreads), 0, s, ra);
+  else hipLaunchKernelGGL(k_roots<O>, dim3(shallow), dim3(kCopyThreads), 0, s, ra);
   if (ev) (void)hipEventRecord(ev[3], s);
-  SweepArgs sa{s_log2, J, lmap, P->d_jobs, wbl, P->jobs.size() == 1 ? 1u : 0u,
-               reinterpret_cast<uint8_t* const*>(w + L.ibase), st, 0, 0, 0};
-  auto resolve = [&](uint32_t b0, uint32_t b1, bool all) {
-    if (b0 == b1) return;
-    // a wave per chunk of map words
-    const uint64_t waves = (uint64_t(b1 - b0) << (s_log2 - 6)) / (all ? kAllChunk : kFewChunk);
-    const uint32_t grid = std::max(1u, uint32_t(std::min<uint64_t>((waves + 3) / 4, kSweepGrid)));
-    const dim3 sgrid((grid + kXcds - 1) / kXcds * kXcds);
-    sa.b0 = b0, sa.b1 = b1, sa.settled = 0;
-    if (all) hipLaunchKernelGGL(k_sweep<true>, sgrid, dim3(kCopyThreads), 0, s, sa);
-    else hipLaunchKernelGGL(k_sweep<false>, sgrid, dim3(kCopyThreads), 0, s, sa);
-    const uint64_t line = P->jobs.size() == 1 ? kPartPositions : kPartPositionsBatch;
-    const uint32_t parts = all && uint64_t(b1 - b0) << s_log2 >= line ? kXcds : 1;
-    for (uint32_t k = 0; k < parts; ++k) {
-      sa.b0 = b0 + uint32_t(uint64_t(b1 - b0) * k / parts), sa.b1 = b0 + uint32_t(uint64_t(b1 - b0) * (k + 1) / parts);
-      sa.settled = parts > 1;
-      if (all) hipLaunchKernelGGL(k_finish<true>, dim3(grid), dim3(kCopyThreads), 0, s, sa);
-      else hipLaunchKernelGGL(k_finish<false>, dim3(grid), dim3(kCopyThreads), 0, s, sa);
-    }
+  const SweepArgs sa{s_log2, J, lmap, P->d_jobs, wbl, P->jobs.size() == 1 ? 1u : 0u,
+                     reinterpret_cast<uint8_t* const*>(w + L.ibase), st, 0, 0, 0};
+  auto part_of = [&](uint32_t b0, uint32_t b1, bool settled) {
+    SweepArgs p = sa;
+    p.b0 = b0, p.b1 = b1, p.settled = settled;
+    return p;
   };
-  resolve(0, W.deep, true);
-  resolve(W.deep, W.items, false);
+  // workgroups of a sweep or finish over n blocks: a wave per chunk of map words
+  auto grid_of = [&](uint32_t n, uint32_t chunk) {
+    const uint64_t waves = (uint64_t(n) << (s_log2 - 6)) / chunk;
+    return std::max(1u, uint32_t(std::min<uint64_t>((waves + 3) / 4, kSweepGrid)));
+  };
+  auto whole = [](uint32_t grid) { return (grid + kXcds - 1) / kXcds * kXcds; };
+  const uint32_t g_all = W.deep ? grid_of(W.deep, kAllChunk) : 0, g_few = shallow ? grid_of(shallow, kFewChunk) : 0;
+  const SweepArgs all = part_of(0, W.deep, false), few = part_of(W.deep, W.items, false);
+  if (both)
+    hipLaunchKernelGGL(k_sweep_both, dim3(whole(g_few) + whole(g_all)), dim3(kCopyThreads), 0, s, few, all, whole(g_few));
+  else if (W.deep) hipLaunchKernelGGL(k_sweep<true>, dim3(whole(g_all)), dim3(kCopyThreads), 0, s, all);
+  else hipLaunchKernelGGL(k_sweep<false>, dim3(whole(g_few)), dim3(kCopyThreads), 0, s, few);
+  const uint64_t line = P->jobs.size() == 1 ? kPartPositions : kPartPositionsBatch;
+  if (uint64_t(W.deep) << s_log2 >= line) {
+    for (uint32_t k = 0; k < kXcds; ++k)
+      hipLaunchKernelGGL(k_finish<true>, dim3(g_all), dim3(kCopyThreads), 0, s,
+                         part_of(uint32_t(uint64_t(W.deep) * k / kXcds), uint32_t(uint64_t(W.deep) * (k + 1) / kXcds), true));
+    if (shallow) hipLaunchKernelGGL(k_finish<false>, dim3(g_few), dim3(kCopyThreads), 0, s, few);
+  } else if (both) {
+    hipLaunchKernelGGL(k_finish_both, dim3(g_few + g_all), dim3(kCopyThreads), 0, s, few, all, g_few);
+  } else if (W.deep) {
+    hipLaunchKernelGGL(k_finish<true>, dim3(g_all), dim3(kCopyThreads), 0, s, all);
+  } else {
+    hipLaunchKernelGGL(k_finish<false>, dim3(g_few), dim3(kCopyThreads), 0, s, few);
+  }
 }
 
 // Enqueue the plan's kernels on s (also used inside a graph capture).
