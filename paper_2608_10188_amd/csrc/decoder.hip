@@ -6,12 +6,12 @@
 //            length, offset and command streams with the slot table in LDS;
 //            renormalisation words are handed to the lanes that need them by
 //            ballot + prefix count over a register window of the word stream.
-//   k_parse  one workgroup per block: commands are parsed 256 at a time by
+//   k_parse  one workgroup per block: commands are parsed 256 to 1024 at a time by
 //            block-wide prefix scans (positions, literal positions, value
 //            indices; DPP moves inside the wave) and an associative scan of
 //            the four-entry distance history (each command is a map on
-//            history tuples); literal runs are placed into an LDS tile that
-//            is written out with 16-byte stores; matches become tokens
+//            history tuples); literal runs leave as whole 16-byte groups of
+//            the output, zeros where matches will be; matches become tokens
 //            (src, dst, len).
 //   match layer: every token (src, dst, len) is a periodic fill
 //            out[dst+k] = out[src + k mod dist] (periodic-fill section).  Two
@@ -177,7 +177,6 @@ __device__ inline uint32_t lanes_below(uint64_t mask) {
 }
 
 __device__ inline uint32_t ld32(const uint8_t* p) { return *reinterpret_cast<const uint32_t*>(p); }
-__device__ inline uint64_t ld64(const uint8_t* p) { return *reinterpret_cast<const uint64_t*>(p); }
 
 // ------------------------------------------------------------------ k_ans --
 
@@ -2403,7 +2402,7 @@ __global__ __launch_bounds__(kCopyThreads) void k_jgather(JumpArgs a) {
 // every walk would end so, and all bytes are marked at once (k_mark).
 //
 // Against the rounds schedule (same data, whole match layer): 254 MB DNA
-// 512 -> 330 us, 80 MiB text 1632 -> 600 us, 64 KiB DNA 122 -> 23 us.
+// 512 -> 330 us, 80 MiB text 1632 -> 565 us, 64 KiB DNA 122 -> 22 us.
 //
 // A block's window position o of window block x is x * S + o, as for the
 // pointer-jumping remainder of the rounds schedule, whose jump array (kJRes
@@ -2636,9 +2635,9 @@ __device__ inline void tile_or(uint32_t* tile, uint32_t at, B16 v) {
 // cut into items of kRootItem bytes, laid end to end over the wave's lanes;
 // the rest of a self-overlapping token repeats them (periodic fill) from the
 // tile.  (With five, six or eight waves a block the decode of 254 MB DNA takes
-// 790 to 804 us instead of 724.)  The tile starts zeroed and the parse left zeros where matches go, so
-// a 16-byte chunk of the block is finished by OR-ing the tile into it, and
-// chunks without match bytes are not touched.
+// 790 to 804 us instead of 724.)  The tile starts zeroed and the parse left
+// zeros where matches go, so a 16-byte chunk of the block is finished by OR-ing
+// the tile into it, and chunks without match bytes are not touched.
 template <class O>
 __device__ __forceinline__ void roots_block(const RootArgs& a, uint32_t block, uint32_t blocks) {
   __shared__ __attribute__((aligned(16))) uint32_t tile[kMaxB / 4 + 4];  // the last item's fifth word
@@ -2857,9 +2856,9 @@ __global__ __launch_bounds__(kCopyThreads) void k_mark(RootArgs a) {
 // A window of deep and other archives takes both at once (the first n_roots
 // workgroups walk), and so its sweeps and finishes: neither kind waits for the
 // other's last workgroups.  40 archives of 61 MiB in all, 16.4 of them deep, 443
-// us with a launch per kind, 407 with one for both (marking still by itself 419;
-// half the sweep's workgroups for each kind 432, the deep ones first 412).  Seven
-// waves a SIMD: the two bodies in one kernel spill with eight.
+// us with a launch per kind, 407 with one for both (deep ones first 412; half the
+// sweep's workgroups for each kind 432, and with marking and walks apart 443).
+// Seven waves a SIMD: the two bodies in one kernel spill with eight.
 template <class O>
 __global__ __launch_bounds__(kCopyThreads, 7) void k_settle(RootArgs a, uint32_t n_roots) {
   if (blockIdx.x < n_roots) roots_block<O>(a, blockIdx.x, n_roots);
@@ -3371,8 +3370,10 @@ static uint32_t jump_pass_bound(uint64_t tok) {
 // costs four bytes of jump array per position, so where few bytes are copied
 // walks win (254 MB DNA, ratio 2.55: 787 against 1660 us; 32 MiB reads, 1.76:
 // 262 against 281 us).  In small plans the marking is cheap and its shorter
-// chain of loads counts: 64 KiB / 4 MiB DNA 94 / 122 us against 140 / 148 us;
-// at 16 MiB the walks win again (172 against 191 us).
+// chain of loads counts: 64 KiB / 4 MiB DNA 94 / 122 us against 140 / 148 us.
+// Between 8 and 16 MiB it depends on the data: 12 MiB of DNA 121 us marked and
+// 136 walked, but 16 MiB of protein 120 and 104, 10 MiB of DNA in 4 KiB blocks
+// 140 and 115.
 constexpr uint64_t kDeepRatio = 3;
 constexpr uint64_t kDeepSmall = 8u << 20;  // positions of a small plan
 // Deep blocks of so many positions are finished run by run (eight launches, each
