@@ -114,7 +114,7 @@ struct JobDev {
   // a range decode's compact scratch: block b's bytes at out + slot[b] * B;
   // a slot of `junk` or more means the junk block (blocks the plan does not
   // decode; only bytes nobody needs are read from it).  null: absolute.
-  const uint32_t* slot;
+  uint32_t* slot;
   uint32_t junk;
 };
 
@@ -3139,13 +3139,6 @@ __global__ __launch_bounds__(kCopyThreads) void k_finish_both(SweepArgs few, Swe
   else finish_part<true>(all, blockIdx.x - n_few, gridDim.x - n_few, queues);
 }
 
-// A range decode's slot table: the window's blocks (one window) take slots
-// 0, 1, ... in window order.
-__global__ void k_slots(uint32_t* slot, const WinBlock* wbl, uint32_t n_items) {
-  for (uint32_t x = blockIdx.x * blockDim.x + threadIdx.x; x < n_items; x += gridDim.x * blockDim.x)
-    slot[wbl[x].b] = x;
-}
-
 // Zero two word ranges (one launch for both).
 // The tokens round 0 left: the sum of its sublist counters (one wave).
 __global__ void k_pending0(const uint32_t* cnt, DevStatus* st) {
@@ -3176,7 +3169,9 @@ __global__ void k_window_init(DevStatus* st, int first) {
 // launch before its entropy stage: the status words, the list counters and
 // pass flags, the persistent chase's leftover bitmap, and for pointer
 // jumping the leftover map (the last round sets its bits) and where every
-// window block's output bytes start.
+// window block's output bytes start.  In a mapped plan (one window) also the
+// slot table: its blocks take slots 0, 1, ... in window order (as a launch of
+// its own: one 16 KiB range 83, now 81 us, 32 mixed ranges 345, now 325).
 struct PrepArgs {
   DevStatus* st;
   int first;
@@ -3199,11 +3194,13 @@ __global__ __launch_bounds__(kCopyThreads) void k_window_prep(PrepArgs a) {
   for (uint64_t i = i0; i < a.n_counts; i += step) a.counts[i] = 0;
   for (uint64_t i = i0; i < a.n_pbits; i += step) a.pbits[i] = 0;
   for (uint64_t i = i0; i < a.n_lmap; i += step) a.lmap[i] = 0;
-  if (!a.ibase) return;
+  constexpr bool kMapped = std::is_same<O, OutMapped>::value;
+  if (!kMapped && !a.ibase) return;
   for (uint64_t x = i0; x < a.n_items; x += step) {
     const WinBlock wb = a.wbl[x];
     const JobDev& jd = a.jobs[wb.job];
-    a.ibase[x] = (uint8_t*)(O(jd).at(wb.b * jd.B));
+    if (kMapped) gp(jd.slot)[wb.b] = uint32_t(x);
+    if (a.ibase) a.ibase[x] = kMapped ? jd.out + x * jd.B : (uint8_t*)(O(jd).at(wb.b * jd.B));
   }
 }
 
@@ -3604,13 +3601,8 @@ uint64_t plan_workspace_for(const aceapex_decoder* d, uint64_t max_blocks, uint6
 
 void plan_copy_options(Plan* dst, const Plan* src) { dst->opt = src->opt; }
 
-int plan_set_slots(Plan* P, uint32_t* slot, hipStream_t s) {
-  if (P->wins.size() > 1) return fail(AX_E_CAPACITY, "a mapped plan holds one window");
-  if (P->wins.empty()) return AX_OK;
-  const uint32_t n = P->wins[0].items;
-  hipLaunchKernelGGL(k_slots, dim3((n + 255) / 256), dim3(256), 0, s, slot, P->d_wbl, n);
-  hipError_t e = hipGetLastError();
-  return e == hipSuccess ? AX_OK : hip_fail(e, "slot table");
+int plan_check_mapped(const Plan* P) {
+  return P->wins.size() > 1 ? fail(AX_E_CAPACITY, "a mapped plan holds one window") : AX_OK;
 }
 bool plan_roots(const Plan* P) { return roots_schedule(P, AX_COPY_PERIODIC); }
 void plan_set_learn(Plan* P, bool learn) { P->learn = learn; }

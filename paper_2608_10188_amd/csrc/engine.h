@@ -30,8 +30,8 @@ struct PlanOptions {
 // One archive to decode: all blocks (blocks empty) or the listed blocks
 // (ascending).  Its bytes land in out at their absolute positions, or, when
 // slot is set (a plan of one job and one window), block b's bytes at
-// out + slot[b] * B with the listed blocks in slots 0, 1, ... (plan_set_slots
-// writes those entries) and any slot >= junk meaning the junk block.
+// out + slot[b] * B with the listed blocks in slots 0, 1, ... (a decode
+// writes those entries first) and any slot >= junk meaning the junk block.
 struct JobSpec {
   const aceapex_decoder* dec;
   uint8_t* out;
@@ -55,8 +55,8 @@ uint64_t plan_workspace_for(const aceapex_decoder* d, uint64_t max_blocks, uint6
 void plan_copy_options(Plan* dst, const Plan* src);
 // Whether the plan's options leave its match layer to the default schedule.
 bool plan_roots(const Plan* p);
-// Enqueue the slot-table entries of a mapped plan's blocks on s.
-int plan_set_slots(Plan* p, uint32_t* slot, hipStream_t s);
+// Refuses a plan with a slot table and more than one window.
+int plan_check_mapped(const Plan* p);
 // Whether a plan learns its jump-pass counts from its own decodes (on by
 // default; off for plans rebuilt for every call).
 void plan_set_learn(Plan* p, bool learn);

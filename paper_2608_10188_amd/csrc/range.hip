@@ -439,7 +439,7 @@ int run_ranges(aceapex_range_plan* rp, const RangeLayout& lay, uint32_t n, const
       (void)ax::plan_get_option(d->plan, AX_OPT_RANGE_JUMP_TOKENS, &jump_from);
       rc = ax::plan_set_option(rp->plan, AX_OPT_TAIL_MODE, int64_t(tok) >= jump_from ? 0 : 1);
     }
-    if (!rc) rc = ax::plan_set_slots(rp->plan, slot, s);
+    if (!rc) rc = ax::plan_check_mapped(rp->plan);
     if (!rc) rc = ax::plan_run(rp->plan, d_work, lay.plan, copy_mode, s);
     if (rc) return rc;
   }
