@@ -2888,7 +2888,10 @@ constexpr uint32_t kSweepRows = 8;     // map words a wave follows at a time whe
 // in 4 KiB blocks 166 / 161 / 155 us).
 constexpr uint32_t kAllChunk = 8, kFewChunk = 4;
 constexpr uint32_t kSweepGrid = 2048;  // workgroups of a sweep or finish launch
-constexpr uint32_t kFinishWords = 4;   // map words a wave of k_finish has in flight (80 MiB text with 8: 701, not 677 us)
+// Map words a wave of k_finish has in flight (80 MiB text with 8: 701, not 677
+// us), and takes at a time: dealing them out evenly counts for more than rows
+// (with the sweep's eight: 80 MiB text 675, not 663 us, 1 MB 65.7, not 61.3).
+constexpr uint32_t kFinishWords = 4;
 constexpr uint32_t kFinishLimit = 1u << 24;  // hops k_finish follows before it reports a device error
 
 struct SweepArgs {
@@ -3037,7 +3040,7 @@ __device__ __forceinline__ void finish_part(const SweepArgs& a, uint32_t block, 
   const uint64_t n = uint64_t(a.b1 - a.b0) << wl;
   const uint32_t sub = lane >> 4, q4 = 4 * (lane & 15u);
   for (uint64_t i = 0; i * 64 * waves < n; ++i) {
-    const uint32_t cnt = queue_words<kAll ? kAllChunk : kFewChunk>(a.lmap, uint64_t(a.b0) << wl, n, wave, waves, i, q);
+    const uint32_t cnt = queue_words<kFinishWords>(a.lmap, uint64_t(a.b0) << wl, n, wave, waves, i, q);
     for (uint32_t c = 0; c < cnt; c += kFinishWords) {
       constexpr uint32_t kRows = kFinishWords / 4;  // a lane's groups: word c + 4 h + lane / 16
       uint32_t bits[kRows], p[kRows];
@@ -3870,15 +3873,16 @@ static void enqueue_roots(Plan* P, const Plan::Win& W, const WinBlock* wbl, uint
   else if (W.deep) hipLaunchKernelGGL(k_sweep<true>, dim3(whole(g_all)), dim3(kCopyThreads), 0, s, all);
   else hipLaunchKernelGGL(k_sweep<false>, dim3(whole(g_few)), dim3(kCopyThreads), 0, s, few);
   const uint64_t line = P->jobs.size() == 1 ? kPartPositions : kPartPositionsBatch;
+  const uint32_t f_all = W.deep ? grid_of(W.deep, kFinishWords) : 0;
   if (uint64_t(W.deep) << s_log2 >= line) {
     for (uint32_t k = 0; k < kXcds; ++k)
-      hipLaunchKernelGGL(k_finish<true>, dim3(g_all), dim3(kCopyThreads), 0, s,
+      hipLaunchKernelGGL(k_finish<true>, dim3(f_all), dim3(kCopyThreads), 0, s,
                          part_of(uint32_t(uint64_t(W.deep) * k / kXcds), uint32_t(uint64_t(W.deep) * (k + 1) / kXcds), true));
     if (shallow) hipLaunchKernelGGL(k_finish<false>, dim3(g_few), dim3(kCopyThreads), 0, s, few);
   } else if (both) {
-    hipLaunchKernelGGL(k_finish_both, dim3(g_few + g_all), dim3(kCopyThreads), 0, s, few, all, g_few);
+    hipLaunchKernelGGL(k_finish_both, dim3(g_few + f_all), dim3(kCopyThreads), 0, s, few, all, g_few);
   } else if (W.deep) {
-    hipLaunchKernelGGL(k_finish<true>, dim3(g_all), dim3(kCopyThreads), 0, s, all);
+    hipLaunchKernelGGL(k_finish<true>, dim3(f_all), dim3(kCopyThreads), 0, s, all);
   } else {
     hipLaunchKernelGGL(k_finish<false>, dim3(g_few), dim3(kCopyThreads), 0, s, few);
   }
