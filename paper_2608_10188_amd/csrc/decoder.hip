@@ -2884,9 +2884,10 @@ constexpr uint32_t kSweepSlots = 4;    // bytes a lane follows at a time
 constexpr uint32_t kSweepRows = 8;     // map words a wave follows at a time where every byte has an entry
 // Consecutive map words a wave takes at a time: rows of whole words where every
 // byte has an entry (80 MiB text with 8 / 4 / 2: 733 / 778 / 804 us), fewer
-// where pending bytes come in clusters (254 MB DNA 718 / 711 / 711 us, 16 MiB
-// in 4 KiB blocks 166 / 161 / 155 us).
-constexpr uint32_t kAllChunk = 8, kFewChunk = 4;
+// where pending bytes come in clusters (with 4 / 2 / 1: 16 MiB of DNA in 4 KiB
+// blocks 151 / 145 / 145 us, 32 MiB of reads 226 / 222 / 223, 254 MB of DNA 685 /
+// 680 / 686).
+constexpr uint32_t kAllChunk = 8, kFewChunk = 2;
 constexpr uint32_t kSweepGrid = 2048;  // workgroups of a sweep or finish launch
 // Map words a wave of k_finish has in flight (80 MiB text with 8: 701, not 677
 // us), and takes at a time: dealing them out evenly counts for more than rows
