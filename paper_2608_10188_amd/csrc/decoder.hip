@@ -2874,8 +2874,9 @@ __global__ __launch_bounds__(kCopyThreads, 7) void k_settle(RootArgs a, uint32_t
 // writes what it found back (a pass of pointer jumping reads and writes every
 // entry and only triples its reach: 80 MiB of text took five, 944 us, where
 // the sweep takes 243 us).  Entries name lower positions, so a walk soon
-// meets bytes that were swept before and carry their own walk's end: only
-// the bytes in flight are followed hop by hop, whatever the chain's length.
+// meets bytes that were swept before and carry their own walk's end; the bytes
+// in flight write back where they stand every few hops (kSweepBack), so that
+// they shorten each other's walks as well.
 // (Stale entries, from another compute unit's cache, name the same value and
 // only cost hops.)  After it, an entry holds its value or names a byte of an
 // earlier run; k_finish writes the bytes, following those.
@@ -2893,7 +2894,16 @@ constexpr uint32_t kSweepGrid = 2048;  // workgroups of a sweep or finish launch
 // us), and takes at a time: dealing them out evenly counts for more than rows
 // (with the sweep's eight: 80 MiB text 675, not 663 us, 1 MB 65.7, not 61.3).
 constexpr uint32_t kFinishWords = 4;
+// Hops after which a sweep writes back where its walks stand.  Other walks then
+// skip what these have followed, so a chain of h bytes in flight at once takes
+// about kSweepBack * log(h) / log(kSweepBack) hops, not h.  Matches that copy from
+// just behind are such chains: rows of 16 bytes, each but four of them a copy of
+// the row before, 4 and 32 MiB: 736 and 2202 us without writing back, 131 and
+// 1149 every 16 hops, 116 and 975 every 8, 108 and 844 every 4.  Text, DNA and
+// reads (chains of long hops) measure the same with all of them.
+constexpr uint32_t kSweepBack = 4;
 constexpr uint32_t kFinishLimit = 1u << 24;  // hops k_finish follows before it reports a device error
+constexpr uint32_t kSweepLimit = 1u << 28;   // the same for a sweep: a run has at most so many positions, and a hop goes down
 
 struct SweepArgs {
   uint32_t s_log2;
@@ -2972,7 +2982,7 @@ __device__ __forceinline__ void sweep_run(const SweepArgs& a, uint32_t block, ui
           v[u] = in[u] ? J[q.g[c + u] * 64 + lane] : kJRes;
           was[u] = v[u];
         }
-        for (;;) {
+        for (uint32_t hop = 1;; ++hop) {
           bool more = false;
 #pragma unroll
           for (uint32_t u = 0; u < kSweepRows; ++u)
@@ -2980,6 +2990,14 @@ __device__ __forceinline__ void sweep_run(const SweepArgs& a, uint32_t block, ui
 #pragma unroll
           for (uint32_t u = 0; u < kSweepRows; ++u) more |= !(v[u] & kJRes) && v[u] >= lo;
           if (!__ballot(more)) break;
+          if (hop % kSweepBack) continue;
+          if (hop >= kSweepLimit) {
+            if (lane == 0) report(a.st, AX_E_DEVICE, ~0ull);
+            return;
+          }
+#pragma unroll
+          for (uint32_t u = 0; u < kSweepRows; ++u)
+            if (v[u] != was[u]) J[q.g[c + u] * 64 + lane] = was[u] = v[u];
         }
 #pragma unroll
         for (uint32_t u = 0; u < kSweepRows; ++u)
@@ -2992,7 +3010,7 @@ __device__ __forceinline__ void sweep_run(const SweepArgs& a, uint32_t block, ui
     uint32_t p[kSweepSlots], v[kSweepSlots], nx[kSweepSlots];  // byte (or none), where its walk is, next word
 #pragma unroll
     for (uint32_t u = 0; u < kSweepSlots; ++u) p[u] = ~0u, v[u] = 0, nx[u] = u;
-    for (;;) {
+    for (uint32_t hop = 1;; ++hop) {
       bool busy = false;
 #pragma unroll
       for (uint32_t u = 0; u < kSweepSlots; ++u) {
@@ -3003,6 +3021,10 @@ __device__ __forceinline__ void sweep_run(const SweepArgs& a, uint32_t block, ui
         busy |= p[u] != ~0u || nx[u] < cnt;
       }
       if (!__ballot(busy)) break;
+      if (hop >= kSweepLimit) {
+        if (lane == 0) report(a.st, AX_E_DEVICE, ~0ull);
+        return;
+      }
       uint32_t jn[kSweepSlots];
       uint64_t w[kSweepSlots];
 #pragma unroll
@@ -3018,6 +3040,8 @@ __device__ __forceinline__ void sweep_run(const SweepArgs& a, uint32_t block, ui
         if ((v[u] & kJRes) || v[u] < lo) {
           J[p[u]] = v[u];
           p[u] = ~0u;
+        } else if (hop % kSweepBack == 0) {
+          J[p[u]] = v[u];
         }
       }
     }
