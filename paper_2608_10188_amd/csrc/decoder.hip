@@ -84,6 +84,14 @@ constexpr uint8_t kPending = 0xFF;          // done[] value of a token not yet c
 constexpr uint32_t kSub = 64;               // pending-list sublists (one counter each, 256 B apart)
 constexpr uint32_t kCounterStride = 64;     // u32 between two sublist counters
 constexpr uint32_t kMaxRoundGrid = 4096;    // workgroups of a round launch
+// Counters of the match bytes of a window's open blocks (one takes 6 ns an
+// addition: 4096 blocks' parse 34, with it 59 us).
+constexpr uint32_t kCopiedShards = 8;
+// A block counts if one byte in so many is copied, repeats of its own bytes not
+// counted: a walk through such a repeat ends at once, and the tile repeats the
+// rest.  Blocks that repeat their first byte, 64 MiB / 1 GiB, marked 369 / 5550 us,
+// walked 253 / 2810.
+constexpr uint32_t kOwnShare = 32;
 // last round: list the leftovers (persistent launch) or mark them for
 // pointer jumping (first entries and leftover-map bits)
 constexpr int kMarkList = 1, kMarkJump = 2;
@@ -99,7 +107,8 @@ struct DevStatus {
   uint32_t jump_used;    // jump passes that found active entries (0: all of them did)
   uint32_t n_jwords;     // leftover-map words with bits set (the jump kernels' work list)
   uint32_t pend0;        // tokens round 0 left to the later rounds (reported when asked)
-  uint32_t pad1[53];
+  uint32_t marked;       // roots, windows with open blocks: the first blocks that k_settle marks
+  uint32_t pad1[52];
 };
 static_assert(sizeof(DevStatus) == 256, "status block is 256 bytes");
 
@@ -530,6 +539,8 @@ struct ParseArgs {
   uint8_t* done;             // per token: kPending until the match layer copies it
   DevStatus* st;
   int write_out;             // 0: tokens only (the token-index build), no output bytes
+  uint32_t open0, open1;     // the window's blocks whose match bytes are counted (Win::open)
+  uint32_t* copied;          // their counters
 };
 
 // History maps.  A command acts on the four-entry distance history as a map
@@ -1068,6 +1079,19 @@ __global__ __launch_bounds__(kT, kT == kParseThreads ? 7 : 4) void k_parse(Parse
     return;
   }
   if (!kRecs) return;
+  if (item >= a.open0 && item < a.open1 && t < 64) {
+    // not those of a block that does little but repeat its own bytes: walks end there at once
+    uint32_t from = 0;
+    if (t < tok_n) {
+      const u64x2 tk = reinterpret_cast<const AX_GLOBAL u64x2*>(gp(a.tok))[tok_lo + t];
+      const uint64_t dist = (tk.y & ((1ull << 48) - 1)) - tk.x;
+      from = uint32_t(tk.y >> 48) + 1;
+      if (tk.x >= bs && dist < from) from = uint32_t(dist);
+    }
+    const uint32_t walked = __builtin_amdgcn_readlane(wave_incl_sum32(from), 63);
+    if (t == 0 && (tok_n > 64 || kOwnShare * walked >= blen))
+      atomicAdd(a.copied + (item % kCopiedShards) * kCounterStride, blen - n_lit);
+  }
   // the records the match layer looks sources up in: two per thread
   const uint64_t cw = t < kMaxB / 64 ? sh.covw[t] : 0, sw = t < kMaxB / 64 ? sh.startw[t] : 0;
   uint64_t all;
@@ -2414,6 +2438,24 @@ constexpr uint32_t kRootItem = 16;   // bytes per work item: one 16-byte source 
 // 262, 792 / 279 us).
 constexpr uint32_t kRootSteps = 9;
 
+// The window's first blocks are marked, the others walked: those of archives
+// taken to be deep, then (open) those of archives that are if enough of their
+// bytes are copies, which their parse has counted by then.
+struct DeepBlocks {
+  uint32_t sure, open;     // blocks
+  uint32_t copied_from;    // match bytes from which the open ones are marked
+  const uint32_t* copied;  // their counters
+  __device__ uint32_t marked() const {
+    if (open == 0) return sure;
+    uint32_t sum = 0;
+#pragma unroll
+    for (uint32_t k = 0; k < kCopiedShards; ++k) sum += copied[k * kCounterStride];
+    return sum >= copied_from ? sure + open : sure;
+  }
+  // what k_settle found
+  __device__ uint32_t marked(const DevStatus* st) const { return open == 0 ? sure : st->marked; }
+};
+
 struct RootArgs {
   const JobDev* jobs;
   const WinBlock* wbl;
@@ -2425,7 +2467,7 @@ struct RootArgs {
   uint32_t* J;            // jump array: one entry per window position
   uint64_t* lmap;         // pending bytes, one bit per window position
   DevStatus* st;
-  uint32_t first;         // k_roots: the window's first block that is not deep
+  DeepBlocks deep;
   uint32_t mark_log2;     // k_mark: log2 of the positions of a workgroup
 };
 
@@ -2639,11 +2681,11 @@ __device__ inline void tile_or(uint32_t* tile, uint32_t at, B16 v) {
 // zeros where matches go, so a 16-byte chunk of the block is finished by OR-ing
 // the tile into it, and chunks without match bytes are not touched.
 template <class O>
-__device__ __forceinline__ void roots_block(const RootArgs& a, uint32_t block, uint32_t blocks) {
+__device__ __forceinline__ void roots_block(const RootArgs& a, uint32_t first, uint32_t block, uint32_t blocks) {
   __shared__ __attribute__((aligned(16))) uint32_t tile[kMaxB / 4 + 4];  // the last item's fifth word
   __shared__ uint64_t row[kMaxB / 64];                                   // the block's pending bytes
   __shared__ uint32_t heads[kCopyThreads];                               // per wave: tokens starting at an item
-  const uint32_t lane = lane_id(), item = a.first + xcd_item(block, blocks);
+  const uint32_t lane = lane_id(), item = first + xcd_item(block, blocks);
   const WinBlock wb = a.wbl[item];
   const uint32_t t1 = item + 1 < a.n_items ? a.wbl[item + 1].tok : a.n_tok;
   const AX_GLOBAL u64x2* const tok = reinterpret_cast<const AX_GLOBAL u64x2*>(gp(a.tok));
@@ -2847,22 +2889,29 @@ __device__ __forceinline__ void mark_part(const RootArgs& a, uint32_t block, uin
 
 template <class O>
 __global__ __launch_bounds__(kCopyThreads, 8) void k_roots(RootArgs a) {
-  roots_block<O>(a, blockIdx.x, gridDim.x);
+  roots_block<O>(a, 0, blockIdx.x, gridDim.x);
 }
 template <class O>
 __global__ __launch_bounds__(kCopyThreads) void k_mark(RootArgs a) {
   mark_part<O>(a, blockIdx.x, gridDim.x);
 }
-// A window of deep and other archives takes both at once (the first n_roots
-// workgroups walk), and so its sweeps and finishes: neither kind waits for the
+// A window of deep and other archives takes both at once (the first workgroups
+// walk), and so its sweeps and finishes: neither kind waits for the
 // other's last workgroups.  40 archives of 61 MiB in all, 16.4 of them deep, 443
 // us with a launch per kind, 407 with one for both (deep ones first 412; half the
 // sweep's workgroups for each kind 432, and with marking and walks apart 443).
-// Seven waves a SIMD: the two bodies in one kernel spill with eight.
+// Seven waves a SIMD: the two bodies in one kernel spill with eight.  With open
+// blocks the grid is that of all of them marked, and walks leave some idle.
 template <class O>
-__global__ __launch_bounds__(kCopyThreads, 7) void k_settle(RootArgs a, uint32_t n_roots) {
-  if (blockIdx.x < n_roots) roots_block<O>(a, blockIdx.x, n_roots);
-  else mark_part<O>(a, blockIdx.x - n_roots, gridDim.x - n_roots);
+__global__ __launch_bounds__(kCopyThreads, 7) void k_settle(RootArgs a) {
+  const uint32_t marked = a.deep.marked(), walked = a.n_items - marked;
+  if (blockIdx.x == 0 && threadIdx.x == 0) a.st->marked = marked;
+  if (blockIdx.x < walked) {
+    roots_block<O>(a, marked, blockIdx.x, walked);
+  } else {
+    const uint32_t part = blockIdx.x - walked, parts = marked << (a.s_log2 - a.mark_log2);
+    if (part < parts) mark_part<O>(a, part, parts);
+  }
 }
 
 // ---- pending bytes: sweep and finish
@@ -2914,8 +2963,9 @@ struct SweepArgs {
   uint32_t one_job;        // 1: the plan has one job, so window positions are contiguous in its output
   uint8_t* const* ibase;   // else per window block: where its output bytes start
   DevStatus* st;
-  uint32_t b0, b1;         // the blocks of this launch
-  uint32_t settled;        // k_finish: the bytes of the blocks before b0 are final
+  uint32_t n_items;
+  DeepBlocks deep;
+  uint32_t part;           // k_finish: this launch's eighth of the marked blocks, those before it final; kXcds: all at once
 };
 
 // Where the bytes of window positions are.
@@ -2959,9 +3009,10 @@ template <bool kAll>
 __device__ __forceinline__ void sweep_run(const SweepArgs& a, uint32_t block, uint32_t blocks, WordQueue* queues) {
   if (a.st->n_pending == 0 || __hip_atomic_load(&a.st->err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) return;
   const uint32_t lane = lane_id(), g = block / kXcds;
-  const uint32_t run = block % kXcds, runs = kXcds;
-  const uint64_t nb = a.b1 - a.b0;
-  const uint32_t b0 = a.b0 + uint32_t(nb * run / runs), b1 = a.b0 + uint32_t(nb * (run + 1) / runs);
+  const uint32_t run = block % kXcds, marked = a.deep.marked(a.st);
+  const uint32_t first = kAll ? 0u : marked;
+  const uint64_t nb = kAll ? marked : a.n_items - marked;
+  const uint32_t b0 = first + uint32_t(nb * run / kXcds), b1 = first + uint32_t(nb * (run + 1) / kXcds);
   const uint32_t lo = b0 << a.s_log2, wl = a.s_log2 - 6;
   AX_GLOBAL uint32_t* const J = gp(a.J);
   const AX_GLOBAL uint64_t* const lm = gp(a.lmap);
@@ -3048,24 +3099,31 @@ __device__ __forceinline__ void sweep_run(const SweepArgs& a, uint32_t block, ui
   }
 }
 
-// The pending bytes of blocks [b0, b1), four consecutive positions a lane: an
-// entry holds the value or names an earlier byte.  With the blocks before b0
-// settled (launches in order) such a byte is read from the output; else the
-// entries are followed to the value, over at most one entry per run.
+// The pending bytes of the marked (kAll) or other blocks, four consecutive
+// positions a lane: an entry holds the value or names an earlier byte.  In
+// launches of an eighth each, in order, such a byte is final by then and read
+// from the output; else the entries are followed to the value, over at most one
+// entry per run.
 template <bool kAll>
 __device__ __forceinline__ void finish_part(const SweepArgs& a, uint32_t block, uint32_t blocks, WordQueue* queues) {
   if (a.st->n_pending == 0 || __hip_atomic_load(&a.st->err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) return;
-  const uint32_t lane = lane_id(), wl = a.s_log2 - 6, lo = a.settled ? a.b0 << a.s_log2 : 0u;
+  const uint32_t marked = a.deep.marked(a.st);
+  uint32_t b0 = kAll ? 0u : marked, b1 = kAll ? marked : a.n_items;
+  if (kAll && a.part < kXcds) {
+    b0 = uint32_t(uint64_t(marked) * a.part / kXcds);
+    b1 = uint32_t(uint64_t(marked) * (a.part + 1) / kXcds);
+  }
+  const uint32_t lane = lane_id(), wl = a.s_log2 - 6, lo = kAll && a.part < kXcds ? b0 << a.s_log2 : 0u;
   const AX_GLOBAL uint32_t* const J = gp(a.J);
   const AX_GLOBAL uint64_t* const lm = gp(a.lmap);
   WordQueue& q = queues[threadIdx.x >> 6];
   const PosOut po(a);
   const uint64_t wave = uint64_t(block) * (kCopyThreads / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint64_t waves = uint64_t(blocks) * (kCopyThreads / 64);
-  const uint64_t n = uint64_t(a.b1 - a.b0) << wl;
+  const uint64_t n = uint64_t(b1 - b0) << wl;
   const uint32_t sub = lane >> 4, q4 = 4 * (lane & 15u);
   for (uint64_t i = 0; i * 64 * waves < n; ++i) {
-    const uint32_t cnt = queue_words<kFinishWords>(a.lmap, uint64_t(a.b0) << wl, n, wave, waves, i, q);
+    const uint32_t cnt = queue_words<kFinishWords>(a.lmap, uint64_t(b0) << wl, n, wave, waves, i, q);
     for (uint32_t c = 0; c < cnt; c += kFinishWords) {
       constexpr uint32_t kRows = kFinishWords / 4;  // a lane's groups: word c + 4 h + lane / 16
       uint32_t bits[kRows], p[kRows];
@@ -3155,19 +3213,18 @@ __global__ __launch_bounds__(kCopyThreads) void k_finish(SweepArgs a) {
   __shared__ WordQueue queues[kCopyThreads / 64];
   finish_part<kAll>(a, blockIdx.x, gridDim.x, queues);
 }
-// both kinds: the first n_few workgroups (a multiple of kXcds) take `few`
-__global__ __launch_bounds__(kCopyThreads) void k_sweep_both(SweepArgs few, SweepArgs all, uint32_t n_few) {
+// both kinds: the first n_few workgroups (of a sweep a multiple of kXcds) take the blocks that are not marked
+__global__ __launch_bounds__(kCopyThreads) void k_sweep_both(SweepArgs a, uint32_t n_few) {
   __shared__ WordQueue queues[kCopyThreads / 64];
-  if (blockIdx.x < n_few) sweep_run<false>(few, blockIdx.x, n_few, queues);
-  else sweep_run<true>(all, blockIdx.x - n_few, gridDim.x - n_few, queues);
+  if (blockIdx.x < n_few) sweep_run<false>(a, blockIdx.x, n_few, queues);
+  else sweep_run<true>(a, blockIdx.x - n_few, gridDim.x - n_few, queues);
 }
-__global__ __launch_bounds__(kCopyThreads) void k_finish_both(SweepArgs few, SweepArgs all, uint32_t n_few) {
+__global__ __launch_bounds__(kCopyThreads) void k_finish_both(SweepArgs a, uint32_t n_few) {
   __shared__ WordQueue queues[kCopyThreads / 64];
-  if (blockIdx.x < n_few) finish_part<false>(few, blockIdx.x, n_few, queues);
-  else finish_part<true>(all, blockIdx.x - n_few, gridDim.x - n_few, queues);
+  if (blockIdx.x < n_few) finish_part<false>(a, blockIdx.x, n_few, queues);
+  else finish_part<true>(a, blockIdx.x - n_few, gridDim.x - n_few, queues);
 }
 
-// Zero two word ranges (one launch for both).
 // The tokens round 0 left: the sum of its sublist counters (one wave).
 __global__ void k_pending0(const uint32_t* cnt, DevStatus* st) {
   uint32_t tot;
@@ -3258,7 +3315,8 @@ struct Plan {
     uint64_t at;       // first WinBlock
     uint32_t items;    // blocks
     uint32_t tok;      // tokens
-    uint32_t deep;     // its first blocks: those of deep archives
+    uint32_t sure, open;  // its first blocks (DeepBlocks)
+    uint64_t open_bytes;  // decoded bytes of the open ones
   };
   std::vector<Win> wins;
   uint32_t max_items = 0, max_tok = 0, slot_b = 0, off_cap = 0, len_cap = 0;
@@ -3389,17 +3447,27 @@ static uint32_t jump_pass_bound(uint64_t tok) {
   return p;
 }
 
-// Archives taken to be deep: those compressed at least kDeepRatio times.  Such
-// ratios need matches over most of the bytes, hence chains (text: 5.2, all
-// bytes marked 764 us for 80 MiB against 1470 us with walks first); marking
-// costs four bytes of jump array per position, so where few bytes are copied
-// walks win (254 MB DNA, ratio 2.55: 787 against 1660 us; 32 MiB reads, 1.76:
-// 262 against 281 us).  In small plans the marking is cheap and its shorter
+// Archives taken to be deep: of a ratio of at least kDeepRatio, with a match per
+// kDenseSpan bytes or more and less than kDenseMatch payload bytes a match (a
+// match costs three to five, so little is left for literals).  Such ratios then
+// come from matches over most of the bytes, hence chains; marking costs four bytes
+// of jump array per position, so where few bytes are copied walks win.  64 MiB
+// marked and walked: text (7 payload bytes a match) 523 and 1288 us, log lines (4)
+// 671 and 2261, rows that repeat the row before (3) 725 and 2392; of less ratio,
+// 254 MB of DNA (2.55) 1660 and 787, 32 MiB of reads (1.76) 281 and 262.
+// Other archives of that ratio may owe it to the entropy coder, and are marked
+// if one byte in kCopiedShare is a copy (open): uniform ACGT (9 %) 394 and 170,
+// with blocks of text for 14 / 27 / 41 % copies 415 and 257, 445 and 379, 466 and
+// 499; zero pages among random ones (72 %) 416 and 540, one page repeated 458 and
+// 911, text with matches of 16 and more 425 and 672.  Asking costs 3 to 6 %.
+// In small plans the marking is cheap and its shorter
 // chain of loads counts: 64 KiB / 4 MiB DNA 94 / 122 us against 140 / 148 us.
 // Between 8 and 16 MiB it depends on the data: 12 MiB of DNA 121 us marked and
 // 136 walked, but 16 MiB of protein 120 and 104, 10 MiB of DNA in 4 KiB blocks
 // 140 and 115.
 constexpr uint64_t kDeepRatio = 3;
+constexpr uint64_t kDenseSpan = 256, kDenseMatch = 12, kBlockOverhead = 64;  // bytes of a block that holds nothing
+constexpr uint64_t kCopiedShare = 3;
 constexpr uint64_t kDeepSmall = 8u << 20;  // positions of a small plan
 // Deep blocks of so many positions are finished run by run (eight launches, each
 // reading settled bytes); fewer in one launch that follows the entries.  Whole
@@ -3442,7 +3510,7 @@ static int build_tables(Plan* P, const std::vector<JobSpec>& specs) {
     P->gtok.reserve(gblocks);
     // windows: consecutive (job, block) items, at most kWindowBlocks blocks
     // and kWindowTokens tokens each
-    Plan::Win cur{0, 0, 0, 0};
+    Plan::Win cur{};
     auto close = [&]() {
       if (!cur.items) return;
       for (uint64_t i = cur.at; i < cur.at + cur.items;) {  // per-job extents inside the window
@@ -3458,15 +3526,21 @@ static int build_tables(Plan* P, const std::vector<JobSpec>& specs) {
       P->max_tok = std::max(P->max_tok, cur.tok);
       P->n_tokens += cur.tok;
       P->wins.push_back(cur);
-      cur = Plan::Win{P->wbl.size(), 0, 0, 0};
+      cur = Plan::Win{};
+      cur.at = P->wbl.size();
     };
-    // jobs enter the windows deep archives first, then densest first (matches
-    // per block): a window runs as long as its deepest dependency chain, and
-    // match-dense archives carry the deep chains, so they share windows
-    // instead of lengthening every one
+    // jobs enter the windows deep archives first, then those that may be, then
+    // densest first (matches per block): a window runs as long as its deepest
+    // dependency chain, and match-dense archives carry the deep chains, so they
+    // share windows instead of lengthening every one
     const bool small = gblocks * P->slot_b <= kDeepSmall;
-    auto deep = [&](size_t j) {
-      return small || specs[j].dec->info.payload_bytes < specs[j].dec->info.n_bytes / kDeepRatio;
+    auto shallow = [&](size_t j) {  // 0 deep, 1 open, 2 not
+      const aceapex_info& I = specs[j].dec->info;
+      if (small) return 0;
+      if (I.payload_bytes >= I.n_bytes / kDeepRatio) return 2;
+      const bool dense = I.n_matches >= I.n_bytes / kDenseSpan &&
+                         I.payload_bytes < I.n_blocks * kBlockOverhead + I.n_matches * kDenseMatch;
+      return dense ? 0 : 1;
     };
     std::vector<size_t> order(specs.size());
     for (size_t j = 0; j < order.size(); ++j) order[j] = j;
@@ -3475,11 +3549,12 @@ static int build_tables(Plan* P, const std::vector<JobSpec>& specs) {
       return d->info.n_blocks ? double(d->mpre[d->info.n_blocks]) / double(d->info.n_blocks) : 0.0;
     };
     std::stable_sort(order.begin(), order.end(), [&](size_t x, size_t y) {
-      return deep(x) != deep(y) ? deep(x) : density(x) > density(y);
+      return shallow(x) != shallow(y) ? shallow(x) < shallow(y) : density(x) > density(y);
     });
     for (const size_t j : order) {
       const aceapex_decoder* d = specs[j].dec;
       const uint64_t nb = specs[j].blocks.empty() ? d->info.n_blocks : specs[j].blocks.size();
+      const int kind = shallow(j);
       for (uint64_t i = 0; i < nb; ++i) {
         const uint64_t b = specs[j].blocks.empty() ? i : specs[j].blocks[i];
         if (b >= d->info.n_blocks) return fail(AX_E_RANGE, "block outside the archive");
@@ -3488,7 +3563,9 @@ static int build_tables(Plan* P, const std::vector<JobSpec>& specs) {
         P->wbl.push_back(WinBlock{b, uint32_t(j), cur.tok, 0, 0});
         P->gtok.push_back(d->mpre[b]);
         cur.items++;
-        cur.deep += deep(j);
+        cur.sure += kind == 0;
+        cur.open += kind == 1;
+        if (kind == 1) cur.open_bytes += std::min<uint64_t>(d->info.block_size, d->info.n_bytes - b * d->info.block_size);
         cur.tok += uint32_t(nt);
       }
     }
@@ -3868,48 +3945,44 @@ static void enqueue_roots(Plan* P, const Plan::Win& W, const WinBlock* wbl, uint
   const uint32_t s_log2 = uint32_t(__builtin_ctz(P->slot_b));
   uint32_t* J = reinterpret_cast<uint32_t*>(w + L.lit);  // the stream slots, dead once the parse is through
   uint64_t* lmap = reinterpret_cast<uint64_t*>(w + L.lmap);
+  const uint32_t deep = W.sure + W.open, walks = W.items - W.sure;  // marked and walked blocks, the open ones in both
+  const DeepBlocks db{W.sure, W.open, uint32_t(W.open_bytes / kCopiedShare), reinterpret_cast<const uint32_t*>(w + L.counts)};
   const RootArgs ra{P->d_jobs, wbl, W.items, W.tok, s_log2, reinterpret_cast<const uint64_t*>(w + L.tok), w + L.cmd,
-                    J, lmap, st, W.deep,
-                    uint64_t(W.deep) << s_log2 <= kDeepSmall ? kMarkSmallLog2 : kMarkLog2};
-  const uint32_t shallow = W.items - W.deep;
-  const uint32_t marks = W.deep << (s_log2 - ra.mark_log2);
-  const bool both = W.deep && shallow;
-  if (both) hipLaunchKernelGGL(k_settle<O>, dim3(shallow + marks), dim3(kCopyThreads), 0, s, ra, shallow);
-  else if (W.deep) hipLaunchKernelGGL(k_mark<O>, dim3(marks), dim3(kCopyThreads), 0, s, ra);
-  else hipLaunchKernelGGL(k_roots<O>, dim3(shallow), dim3(kCopyThreads), 0, s, ra);
+                    J, lmap, st, db, uint64_t(deep) << s_log2 <= kDeepSmall ? kMarkSmallLog2 : kMarkLog2};
+  const uint32_t marks = deep << (s_log2 - ra.mark_log2);
+  const bool both = deep && walks;
+  if (both) hipLaunchKernelGGL(k_settle<O>, dim3(W.items - deep + marks), dim3(kCopyThreads), 0, s, ra);
+  else if (deep) hipLaunchKernelGGL(k_mark<O>, dim3(marks), dim3(kCopyThreads), 0, s, ra);
+  else hipLaunchKernelGGL(k_roots<O>, dim3(walks), dim3(kCopyThreads), 0, s, ra);
   if (ev) (void)hipEventRecord(ev[3], s);
-  const SweepArgs sa{s_log2, J, lmap, P->d_jobs, wbl, P->jobs.size() == 1 ? 1u : 0u,
-                     reinterpret_cast<uint8_t* const*>(w + L.ibase), st, 0, 0, 0};
-  auto part_of = [&](uint32_t b0, uint32_t b1, bool settled) {
-    SweepArgs p = sa;
-    p.b0 = b0, p.b1 = b1, p.settled = settled;
-    return p;
-  };
+  SweepArgs sa{s_log2, J, lmap, P->d_jobs, wbl, P->jobs.size() == 1 ? 1u : 0u,
+               reinterpret_cast<uint8_t* const*>(w + L.ibase), st, W.items, db, kXcds};
   // workgroups of a sweep or finish over n blocks: a wave per chunk of map words
   auto grid_of = [&](uint32_t n, uint32_t chunk) {
     const uint64_t waves = (uint64_t(n) << (s_log2 - 6)) / chunk;
     return std::max(1u, uint32_t(std::min<uint64_t>((waves + 3) / 4, kSweepGrid)));
   };
   auto whole = [](uint32_t grid) { return (grid + kXcds - 1) / kXcds * kXcds; };
-  const uint32_t g_all = W.deep ? grid_of(W.deep, kAllChunk) : 0, g_few = shallow ? grid_of(shallow, kFewChunk) : 0;
-  const SweepArgs all = part_of(0, W.deep, false), few = part_of(W.deep, W.items, false);
-  if (both)
-    hipLaunchKernelGGL(k_sweep_both, dim3(whole(g_few) + whole(g_all)), dim3(kCopyThreads), 0, s, few, all, whole(g_few));
-  else if (W.deep) hipLaunchKernelGGL(k_sweep<true>, dim3(whole(g_all)), dim3(kCopyThreads), 0, s, all);
-  else hipLaunchKernelGGL(k_sweep<false>, dim3(whole(g_few)), dim3(kCopyThreads), 0, s, few);
+  const uint32_t g_all = deep ? whole(grid_of(deep, kAllChunk)) : 0;
+  const uint32_t f_few = walks ? grid_of(walks, kFewChunk) : 0, g_few = whole(f_few);
+  if (both) hipLaunchKernelGGL(k_sweep_both, dim3(g_few + g_all), dim3(kCopyThreads), 0, s, sa, g_few);
+  else if (deep) hipLaunchKernelGGL(k_sweep<true>, dim3(g_all), dim3(kCopyThreads), 0, s, sa);
+  else hipLaunchKernelGGL(k_sweep<false>, dim3(g_few), dim3(kCopyThreads), 0, s, sa);
   const uint64_t line = P->jobs.size() == 1 ? kPartPositions : kPartPositionsBatch;
-  const uint32_t f_all = W.deep ? grid_of(W.deep, kFinishWords) : 0;
-  if (uint64_t(W.deep) << s_log2 >= line) {
-    for (uint32_t k = 0; k < kXcds; ++k)
-      hipLaunchKernelGGL(k_finish<true>, dim3(f_all), dim3(kCopyThreads), 0, s,
-                         part_of(uint32_t(uint64_t(W.deep) * k / kXcds), uint32_t(uint64_t(W.deep) * (k + 1) / kXcds), true));
-    if (shallow) hipLaunchKernelGGL(k_finish<false>, dim3(g_few), dim3(kCopyThreads), 0, s, few);
+  const uint32_t f_all = deep ? grid_of(deep, kFinishWords) : 0;
+  if (uint64_t(deep) << s_log2 >= line) {
+    for (uint32_t k = 0; k < kXcds; ++k) {
+      SweepArgs part = sa;
+      part.part = k;
+      hipLaunchKernelGGL(k_finish<true>, dim3(f_all), dim3(kCopyThreads), 0, s, part);
+    }
+    if (walks) hipLaunchKernelGGL(k_finish<false>, dim3(f_few), dim3(kCopyThreads), 0, s, sa);
   } else if (both) {
-    hipLaunchKernelGGL(k_finish_both, dim3(g_few + f_all), dim3(kCopyThreads), 0, s, few, all, g_few);
-  } else if (W.deep) {
-    hipLaunchKernelGGL(k_finish<true>, dim3(f_all), dim3(kCopyThreads), 0, s, all);
+    hipLaunchKernelGGL(k_finish_both, dim3(f_few + f_all), dim3(kCopyThreads), 0, s, sa, f_few);
+  } else if (deep) {
+    hipLaunchKernelGGL(k_finish<true>, dim3(f_all), dim3(kCopyThreads), 0, s, sa);
   } else {
-    hipLaunchKernelGGL(k_finish<false>, dim3(g_few), dim3(kCopyThreads), 0, s, few);
+    hipLaunchKernelGGL(k_finish<false>, dim3(f_few), dim3(kCopyThreads), 0, s, sa);
   }
 }
 
@@ -3934,7 +4007,7 @@ static void enqueue_out(Plan* P, uint8_t* w, int copy_mode, hipStream_t s, bool 
     {
       const bool jmap = jump && ntok;
       const uint32_t n_counts = uint32_t((L.jflags - L.counts) / 4 + kJPasses * kJShards * kJFlagStride);
-      const PrepArgs pr{st, int(first), counts, roots ? 0u : n_counts, reinterpret_cast<uint32_t*>(w + L.pbits),
+      const PrepArgs pr{st, int(first), counts, !roots ? n_counts : W.open ? kCopiedShards * kCounterStride : 0u, reinterpret_cast<uint32_t*>(w + L.pbits),
                         ntok && !roots ? n_words : 0u, reinterpret_cast<uint64_t*>(w + L.lmap), jmap && !roots ? mwords : 0u,
                         jmap && !(roots && P->jobs.size() == 1) ? reinterpret_cast<uint8_t**>(w + L.ibase) : nullptr, P->d_jobs,
                         wbl, W.items};
@@ -3951,7 +4024,8 @@ static void enqueue_out(Plan* P, uint8_t* w, int copy_mode, hipStream_t s, bool 
     const bool recs = roots || bulk <= 1;
     ParseArgs pa{P->d_jobs, wbl, W.items, W.tok, P->slot_b, w + L.lit, w + L.cmd, w + L.off, w + L.len, P->off_cap,
                  P->len_cap, reinterpret_cast<const uint32_t*>(w + L.nsym), reinterpret_cast<uint64_t*>(w + L.tok),
-                 roots ? nullptr : reinterpret_cast<uint32_t*>(w + L.tblk), w + L.done, st, 1};
+                 roots ? nullptr : reinterpret_cast<uint32_t*>(w + L.tblk), w + L.done, st, 1,
+                 W.sure, roots ? W.sure + W.open : W.sure, counts};
     if (!recs)
       hipLaunchKernelGGL((k_parse<O, false, kParseThreads>), dim3(W.items), dim3(kParseThreads), 0, s, pa);
     else if (W.items <= kParseWideBlocks)
