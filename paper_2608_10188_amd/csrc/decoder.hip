@@ -3447,26 +3447,28 @@ static uint32_t jump_pass_bound(uint64_t tok) {
   return p;
 }
 
-// Archives taken to be deep: of a ratio of at least kDeepRatio, with a match per
-// kDenseSpan bytes or more and less than kDenseMatch payload bytes a match (a
-// match costs three to five, so little is left for literals).  Such ratios then
-// come from matches over most of the bytes, hence chains; marking costs four bytes
-// of jump array per position, so where few bytes are copied walks win.  64 MiB
-// marked and walked: text (7 payload bytes a match) 523 and 1288 us, log lines (4)
-// 671 and 2261, rows that repeat the row before (3) 725 and 2392; of less ratio,
-// 254 MB of DNA (2.55) 1660 and 787, 32 MiB of reads (1.76) 281 and 262.
-// Other archives of that ratio may owe it to the entropy coder, and are marked
-// if one byte in kCopiedShare is a copy (open): uniform ACGT (9 %) 394 and 170,
-// with blocks of text for 14 / 27 / 41 % copies 415 and 257, 445 and 379, 466 and
-// 499; zero pages among random ones (72 %) 416 and 540, one page repeated 458 and
-// 911, text with matches of 16 and more 425 and 672.  Asking costs 3 to 6 %.
+// Archives taken to be deep: with a match per kDenseSpan bytes or more and less
+// than kDenseMatch payload bytes a match.  A match costs three to five, so little
+// is left for literals, most bytes are copies, and chains follow.  Marking costs
+// four bytes of jump array per position, so where few bytes are copied walks win.
+// 64 MiB marked and walked: text (7 payload bytes a match) 526 and 1279 us, log
+// lines (4) 681 and 2242, rows that repeat the row before (4) 708 and 1831, text
+// with every twentieth byte replaced (8, ratio 2.4) 584 and 1697; DNA (30) 439 and
+// 242, protein (45) 416 and 241, 32 MiB of reads (25) 258 and 238.
+// Of other archives, those of ratio kDeepRatio and more may owe it to the entropy
+// coder, and those under kOpenMatch payload bytes a match may be either; they are
+// marked if one byte in kCopiedShare is a copy (open): uniform ACGT (9 % copies) 394
+// and 170, three symbols (26 %) 495 and 306, ACGT with blocks of text (24 / 36 / 69 %)
+// 441 and 373, 461 and 489, 518 and 1021; log lines with long random fields (53 %)
+// 481 and 985, zero pages among random ones (72 %) 416 and 540, text with matches of
+// 16 and more 425 and 672.  Asking costs 3 to 6 %.
 // In small plans the marking is cheap and its shorter
 // chain of loads counts: 64 KiB / 4 MiB DNA 94 / 122 us against 140 / 148 us.
 // Between 8 and 16 MiB it depends on the data: 12 MiB of DNA 121 us marked and
 // 136 walked, but 16 MiB of protein 120 and 104, 10 MiB of DNA in 4 KiB blocks
 // 140 and 115.
 constexpr uint64_t kDeepRatio = 3;
-constexpr uint64_t kDenseSpan = 256, kDenseMatch = 12, kBlockOverhead = 64;  // bytes of a block that holds nothing
+constexpr uint64_t kDenseSpan = 256, kDenseMatch = 10, kOpenMatch = 20, kBlockOverhead = 64;  // bytes of a block that holds nothing
 constexpr uint64_t kCopiedShare = 3;
 constexpr uint64_t kDeepSmall = 8u << 20;  // positions of a small plan
 // Deep blocks of so many positions are finished run by run (eight launches, each
@@ -3536,11 +3538,11 @@ static int build_tables(Plan* P, const std::vector<JobSpec>& specs) {
     const bool small = gblocks * P->slot_b <= kDeepSmall;
     auto shallow = [&](size_t j) {  // 0 deep, 1 open, 2 not
       const aceapex_info& I = specs[j].dec->info;
-      if (small) return 0;
-      if (I.payload_bytes >= I.n_bytes / kDeepRatio) return 2;
-      const bool dense = I.n_matches >= I.n_bytes / kDenseSpan &&
-                         I.payload_bytes < I.n_blocks * kBlockOverhead + I.n_matches * kDenseMatch;
-      return dense ? 0 : 1;
+      auto dense = [&](uint64_t per) {  // matches all over, at less than `per` payload bytes each
+        return I.n_matches >= I.n_bytes / kDenseSpan && I.payload_bytes < I.n_blocks * kBlockOverhead + I.n_matches * per;
+      };
+      if (small || dense(kDenseMatch)) return 0;
+      return I.payload_bytes < I.n_bytes / kDeepRatio || dense(kOpenMatch) ? 1 : 2;
     };
     std::vector<size_t> order(specs.size());
     for (size_t j = 0; j < order.size(); ++j) order[j] = j;
