@@ -421,7 +421,8 @@ def run_batch(args, log):
         "warmup": args.warmup, "ms_per_step": round(batched_ms, 3), "higher_is_better": True, "scaling": "weak",
         "vs_baseline": None, "dtype": "u8", "data": "synthetic",
         "config": {"workload": f"batch of {count} archives", "n_bytes": total, "archive_bytes": comp,
-                   "autotuned": bool(args.autotune), "bulk_rounds": None if args.autotune else (args.bulk_rounds or 4),
+                   "autotuned": bool(args.autotune), "schedule": None if args.autotune else "rounds" if args.bulk_rounds else "roots",
+                   "bulk_rounds": None if args.autotune else args.bulk_rounds or None,
                    "streams": 1 if args.autotune else args.streams},
         "plain_loop_gbs": round(total / (loop_ms / 1e3) / 1e9, 3), "plain_loop_ms": round(loop_ms, 3),
         "speedup_vs_plain_loop": round(loop_ms / batched_ms, 3), "status": [err, err2],
@@ -575,6 +576,16 @@ def main():
     probe["decoded_frac_of_fill"] = round(value / probe["fill"]["written_gbs"], 5)
     probe["alg_frac_of_copy"] = round(achieved / probe["copy"]["moved_gbs"], 5)
 
+    # the match layer's schedule, and its knobs where it has rounds
+    rounds = bool(args.bulk_rounds or args.fill or args.tail_chunks or args.tail_mode or args.jump_passes
+                  or args.copy == "serial")
+    schedule = {"schedule": "rounds" if rounds else "roots"}
+    knobs = {"bulk_rounds": args.bulk_rounds or "learned, at most 4", "fill": args.fill or "0,0",
+             "tail_chunks": args.tail_chunks or 1,
+             "tail_mode": "chase" if args.tail_mode or args.copy == "serial" else "jump",
+             "jump_passes": args.jump_passes or "auto"}
+    schedule.update({k: v if rounds else None for k, v in knobs.items()})
+
     res = {
         "metric": METRIC, "value": round(value, 3), "unit": "GB/s", "n_gpus": 1, "steps": args.steps,
         "warmup": args.warmup, "ms_per_step": round(ms_per_step, 4), "higher_is_better": True,
@@ -583,9 +594,7 @@ def main():
                    "ratio": round(n / c_bytes, 4), "blocks": int(dec.info.n_blocks),
                    "commands": int(st.n_commands), "matches": int(st.n_matches), "repeats": int(st.n_rep),
                    "copy_mode": args.copy, "no_rep": bool(args.no_rep), "depth_cap": args.depth_cap,
-                   "max_depth": int(st.max_depth) if args.depth_cap else None, "bulk_rounds": args.bulk_rounds or 4, "fill": args.fill or "0,0", "tail_chunks": args.tail_chunks or 1,
-                   "graph": bool(args.graph), "tail_mode": "chase" if args.tail_mode else "jump",
-                   "jump_passes": args.jump_passes or "auto"},
+                   "max_depth": int(st.max_depth) if args.depth_cap else None, "graph": bool(args.graph), **schedule},
         "decoded_frac_of_hbm_peak": round(value / HBM_PEAK_GBS, 5),
         "step_ms": {"min": round(float(step_ms.min()), 4), "median": round(float(np.median(step_ms)), 4),
                     "max": round(float(step_ms.max()), 4)},

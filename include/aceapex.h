@@ -172,20 +172,22 @@ int aceapex_decode_all_static(aceapex_decoder* dec, uint8_t* d_out, uint64_t out
  * recorded around the stages of every window and summed), in milliseconds:
  * entropy (rANS of the four streams), parse (commands, literal placement,
  * token emission), copy (the whole match layer); remainder (nullable) is the
- * part of copy spent on the tokens the bulk rounds left.  Blocks on the
+ * part of copy spent on the tokens the bulk rounds left, or, without rounds, on
+ * the bytes whose chains are followed by window positions.  Blocks on the
  * events. */
 int aceapex_decoder_stage_ms(aceapex_decoder* dec, float* ans_ms, float* parse_ms, float* copy_ms,
                              float* remainder_ms);
 /* 1 = record stage events on later decodes (five event records per window). */
 int aceapex_decoder_set_timing(aceapex_decoder* dec, int enable);
 
-/* Decoder options (schedule knobs; none changes a decoded byte).  With every
- * match-layer knob at its default the match layer follows each match to the
- * literal bytes it comes from, without rounds; AX_OPT_BULK_ROUNDS,
- * AX_OPT_FILL_ROUNDS, AX_OPT_FILL_TAIL, AX_OPT_TAIL_CHUNKS,
- * AX_OPT_ROUND0_TILE, AX_OPT_TAIL_MODE and AX_OPT_JUMP_PASSES describe the
- * level-synchronous schedule, which runs when one of them is set to another
- * value than its default, and in the serial copy mode.
+/* Decoder options (schedule knobs; none changes a decoded byte).  The match
+ * layer follows each match to the literal bytes it comes from, without rounds,
+ * until a knob of the level-synchronous schedule is set, to whatever value:
+ * AX_OPT_BULK_ROUNDS, AX_OPT_FILL_ROUNDS, AX_OPT_FILL_TAIL,
+ * AX_OPT_TAIL_CHUNKS, AX_OPT_ROUND0_TILE, AX_OPT_TAIL_MODE and
+ * AX_OPT_JUMP_PASSES, and for range decodes AX_OPT_RANGE_JUMP_TOKENS, select
+ * that schedule (AX_OPT_SCHEDULE overrides this).  The serial copy mode always
+ * runs it.
  *   AX_OPT_BULK_ROUNDS  number of level-synchronous match-layer rounds (one
  *     launch each, plain cached accesses) before the launches that finish the
  *     deeper tokens, in [1, 250] (default 4).  Until it is set, a decoder
@@ -235,6 +237,11 @@ enum { AX_OPT_JUMP_PASSES = 8 };
  *     by pointer jumping, smaller ones by the persistent launch (default 4096;
  *     0 = always jump). */
 enum { AX_OPT_RANGE_JUMP_TOKENS = 9 };
+/*   AX_OPT_SCHEDULE  the match layer's schedule: 0 = by whether a knob of the
+ *     level-synchronous one has been set (default), 1 = without rounds, the
+ *     knobs keeping their values unused, 2 = level-synchronous, with what the
+ *     knobs say and their defaults. */
+enum { AX_OPT_SCHEDULE = 10 };
 int aceapex_decoder_set_option(aceapex_decoder* dec, int option, int64_t value);
 
 /* The entropy stage alone (Setup: per-block rANS of the LIT, LEN, OFF and

@@ -32,7 +32,8 @@ EXPORTS = [
     "aceapex_closure_sizes",
 ]
 OPT_BULK_ROUNDS, OPT_FILL_ROUNDS, OPT_FILL_TAIL, OPT_TAIL_CHUNKS, OPT_GRAPH, OPT_ROUND0_TILE = 1, 2, 3, 4, 5, 6
-OPT_TAIL_MODE, OPT_JUMP_PASSES, OPT_RANGE_JUMP_TOKENS = 7, 8, 9
+OPT_TAIL_MODE, OPT_JUMP_PASSES, OPT_RANGE_JUMP_TOKENS, OPT_SCHEDULE = 7, 8, 9, 10
+SCHEDULE_AUTO, SCHEDULE_ROOTS, SCHEDULE_ROUNDS = 0, 1, 2
 TAIL_JUMP, TAIL_CHASE = 0, 1
 STATIC_SCRATCH_BYTES = 128 << 20  # AX_STATIC_SCRATCH_BYTES
 

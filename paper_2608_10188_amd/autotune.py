@@ -7,11 +7,12 @@ fastest.  Runs on the device; the caller supplies outputs to compare.
 """
 import itertools
 
-from . import (OPT_BULK_ROUNDS, OPT_FILL_ROUNDS, OPT_FILL_TAIL, OPT_GRAPH, OPT_ROUND0_TILE, OPT_TAIL_CHUNKS,
-               OPT_TAIL_MODE)
+from . import (OPT_BULK_ROUNDS, OPT_FILL_ROUNDS, OPT_FILL_TAIL, OPT_GRAPH, OPT_ROUND0_TILE, OPT_SCHEDULE,
+               OPT_TAIL_CHUNKS, OPT_TAIL_MODE, SCHEDULE_ROOTS, SCHEDULE_ROUNDS)
 
-DEFAULT = {OPT_BULK_ROUNDS: 4, OPT_FILL_ROUNDS: 0, OPT_FILL_TAIL: 0, OPT_TAIL_CHUNKS: 1, OPT_ROUND0_TILE: 1,
-           OPT_TAIL_MODE: 0, OPT_GRAPH: 1}
+DEFAULT = {OPT_SCHEDULE: SCHEDULE_ROOTS, OPT_GRAPH: 1}
+ROUNDS = {OPT_SCHEDULE: SCHEDULE_ROUNDS, OPT_BULK_ROUNDS: 4, OPT_FILL_ROUNDS: 0, OPT_FILL_TAIL: 0, OPT_TAIL_CHUNKS: 1,
+          OPT_ROUND0_TILE: 1, OPT_TAIL_MODE: 0, OPT_GRAPH: 1}
 
 GRID = {
     OPT_BULK_ROUNDS: [1, 2, 4, 8],
@@ -22,9 +23,11 @@ GRID = {
 
 
 def candidates():
+    """The schedule without rounds, then those of the rounds' knobs."""
+    yield dict(DEFAULT)
     keys = list(GRID)
     for vals in itertools.product(*(GRID[k] for k in keys)):
-        c = dict(DEFAULT)
+        c = dict(ROUNDS)
         c.update(zip(keys, vals))
         yield c
 

@@ -3861,9 +3861,15 @@ int plan_set_option(Plan* P, int option, int64_t value) {
       if (value < 0 || value > int64_t(kWindowTokens)) return fail(AX_E_ARG, "range jump tokens out of range");
       P->opt.range_jump_tokens = value;
       break;
+    case AX_OPT_SCHEDULE:
+      if (value < 0 || value > 2) return fail(AX_E_ARG, "schedule must be 0, 1 or 2");
+      P->opt.schedule = int(value);
+      break;
     default:
       return fail(AX_E_ARG, "unknown option");
   }
+  if (option == AX_OPT_RANGE_JUMP_TOKENS) P->opt.range_knob_set = true;
+  else if (option != AX_OPT_GRAPH && option != AX_OPT_SCHEDULE) P->opt.knob_set = true;
   if (P->graph) {  // knobs are baked into a captured graph
     (void)hipGraphExecDestroy(P->graph);
     P->graph = nullptr;
@@ -3882,6 +3888,7 @@ int plan_get_option(const Plan* P, int option, int64_t* value) {
     case AX_OPT_TAIL_MODE: *value = P->opt.tail_mode; return AX_OK;
     case AX_OPT_JUMP_PASSES: *value = P->opt.jump_passes; return AX_OK;
     case AX_OPT_RANGE_JUMP_TOKENS: *value = P->opt.range_jump_tokens; return AX_OK;
+    case AX_OPT_SCHEDULE: *value = P->opt.schedule; return AX_OK;
     default: return fail(AX_E_ARG, "unknown option");
   }
 }
@@ -3928,15 +3935,14 @@ int plan_stage_ms(Plan* P, float* ans, float* parse, float* copy, float* remaind
   return AX_OK;
 }
 
-// Whether a decode runs the roots schedule (k_roots): the default one; any
-// knob of the rounds schedule off its default, or the serial copy mode, asks
-// for the rounds.
+// Whether a decode runs the roots schedule (k_roots): the default one, until the
+// caller sets a knob of the rounds (a value that is the default one included: it
+// asks for so many rounds, not for none) or names the schedule.  The serial copy
+// mode is one of rounds.
 static bool roots_schedule(const Plan* P, int copy_mode) {
-  const PlanOptions d;
   const PlanOptions& o = P->opt;
-  return copy_mode == AX_COPY_PERIODIC && o.bulk_rounds == d.bulk_rounds && o.fill_round == d.fill_round &&
-         o.fill_tail == d.fill_tail && o.tail_chunks == d.tail_chunks && o.round0_tile == d.round0_tile &&
-         o.tail_mode == d.tail_mode && o.jump_passes == d.jump_passes;
+  if (copy_mode != AX_COPY_PERIODIC || o.schedule == 2) return false;
+  return o.schedule == 1 || !(o.knob_set || (P->mapped && o.range_knob_set));
 }
 
 // The roots match layer of one window.

@@ -25,6 +25,9 @@ struct PlanOptions {
   int tail_mode = 0;    // deep remainder: pointer jumping (0) or the persistent chase (1)
   int jump_passes = 0;  // at most this many jump passes per window (0: automatic)
   int64_t range_jump_tokens = 4096;  // range decodes: closures of at least this many matches jump
+  int schedule = 0;          // without rounds (1), with (2), or with once a knob of theirs was set (0)
+  bool knob_set = false;     // one of the rounds' knobs was set, to whatever value
+  bool range_knob_set = false;  // range_jump_tokens was: a knob of range decodes alone
 };
 
 // One archive to decode: all blocks (blocks empty) or the listed blocks
@@ -53,7 +56,7 @@ int plan_reset(Plan* p, const std::vector<JobSpec>& jobs, hipStream_t s);
 // Workspace of a one-window plan of decoder d with these maxima.
 uint64_t plan_workspace_for(const aceapex_decoder* d, uint64_t max_blocks, uint64_t max_tokens);
 void plan_copy_options(Plan* dst, const Plan* src);
-// Whether the plan's options leave its match layer to the default schedule.
+// Whether the plan's match layer runs without rounds.
 bool plan_roots(const Plan* p);
 // Refuses a plan with a slot table and more than one window.
 int plan_check_mapped(const Plan* p);
