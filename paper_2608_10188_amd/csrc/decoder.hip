@@ -73,7 +73,10 @@ constexpr uint32_t kParseThreads = 256;
 // 512 of DNA 116, 106, 110; 768 of DNA 150, 137, 151, of text 140, 136, 148;
 // 1024 of DNA 153, 142, 166 but of text 165, 168, 181, of reads 173, 180, 192 and
 // of 4 KiB blocks 65, 69, 85; 2048 of reads 224, 233, 264; 15500 of DNA 685,
-// 732, 1043.  A compute unit each is the line for 1024, three blocks for 512.
+// 732, 1043.  Of 4 KiB blocks (about a hundred commands of DNA) 64, 256 of DNA 57,
+// 55, 49 and 60, 59, 52, of text 64, 62, 60; with 256 and 512 threads 512 of DNA
+// 65, 62, 768 of DNA 71, 71, of text 78, 83.  A compute unit each is the line for
+// 1024, three blocks for 512.
 constexpr uint32_t kParseWide = 1024, kParseMid = 512;
 constexpr uint32_t kParseWideBlocks = 256, kParseMidBlocks = 768;
 constexpr uint32_t kOffStage = 3072;        // offset-stream bytes staged in LDS by k_parse
@@ -3317,6 +3320,7 @@ struct Plan {
     uint32_t tok;      // tokens
     uint32_t sure, open;  // its first blocks (DeepBlocks)
     uint64_t open_bytes;  // decoded bytes of the open ones
+    uint32_t most;        // most blocks of one archive among them all
   };
   std::vector<Win> wins;
   uint32_t max_items = 0, max_tok = 0, slot_b = 0, off_cap = 0, len_cap = 0;
@@ -3471,13 +3475,15 @@ constexpr uint64_t kDeepRatio = 3;
 constexpr uint64_t kDenseSpan = 256, kDenseMatch = 10, kOpenMatch = 20, kBlockOverhead = 64;  // bytes of a block that holds nothing
 constexpr uint64_t kCopiedShare = 3;
 constexpr uint64_t kDeepSmall = 8u << 20;  // positions of a small plan
-// Deep blocks of so many positions are finished run by run (eight launches, each
-// reading settled bytes); fewer in one launch that follows the entries.  Whole
+// Marked blocks are finished run by run (eight launches, each reading settled
+// bytes) where chains cross several runs: an archive of so many positions, and
+// more than half of the window's.  Otherwise one launch follows the entries.  Whole
 // decodes of text in eight launches and in one: 8 MiB 127 and 110 us, 16 MiB 167
-// and 168, 24 MiB 207 and 227, 32 MiB 250 and 288, with 4, 8 or 16 KiB blocks.
-// Chains end in their own archive, so those of a batch cross fewer runs: 40
-// archives of up to 4 MiB, 16.4 MiB of them deep, 481 and 447.
-constexpr uint64_t kPartPositions = 16u << 20, kPartPositionsBatch = 32u << 20;
+// and 168, 24 MiB 207 and 227, 32 MiB 250 and 288, with 4, 8 or 16 KiB blocks; 24
+// / 80 MiB and a small archive 234 and 245, 690 and 794.  Chains end in their own
+// archive: two / four of 12 MiB 220 and 201, 404 and 369, two of 40 677 and 665,
+// 100 of 1 875 and 849; one of 40 and eight of 4 631 and 638.
+constexpr uint64_t kPartPositions = 16u << 20;
 
 // Host tables of a plan: jobs, window blocks, windows, maxima.
 static int build_tables(Plan* P, const std::vector<JobSpec>& specs) {
@@ -3522,6 +3528,7 @@ static int build_tables(Plan* P, const std::vector<JobSpec>& specs) {
           P->wbl[m].first = uint32_t(i - cur.at);
           P->wbl[m].count = uint32_t(k - i);
         }
+        if (i - cur.at < cur.sure + cur.open) cur.most = std::max(cur.most, uint32_t(k - i));
         i = k;
       }
       P->max_items = std::max(P->max_items, cur.items);
@@ -3976,9 +3983,8 @@ static void enqueue_roots(Plan* P, const Plan::Win& W, const WinBlock* wbl, uint
   if (both) hipLaunchKernelGGL(k_sweep_both, dim3(g_few + g_all), dim3(kCopyThreads), 0, s, sa, g_few);
   else if (deep) hipLaunchKernelGGL(k_sweep<true>, dim3(g_all), dim3(kCopyThreads), 0, s, sa);
   else hipLaunchKernelGGL(k_sweep<false>, dim3(g_few), dim3(kCopyThreads), 0, s, sa);
-  const uint64_t line = P->jobs.size() == 1 ? kPartPositions : kPartPositionsBatch;
   const uint32_t f_all = deep ? grid_of(deep, kFinishWords) : 0;
-  if (uint64_t(deep) << s_log2 >= line) {
+  if (uint64_t(W.most) << s_log2 >= kPartPositions && W.most > deep / 2) {
     for (uint32_t k = 0; k < kXcds; ++k) {
       SweepArgs part = sa;
       part.part = k;

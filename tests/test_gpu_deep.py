@@ -137,6 +137,24 @@ def test_batches_of_kinds(kinds):
                 _same(o.cpu().numpy(), x)
 
 
+@pytest.mark.parametrize("sizes", [(17 << 20, 100000), (17 << 20, 17 << 20), (17 << 20, 8 << 20, 8 << 20),
+                                   (17 << 20, 9 << 20, 9 << 20)])
+def test_finish_of_a_batch(sizes):
+    """One archive with more than half of the marked blocks, with half of them
+    and with fewer: finished in eight launches and in one."""
+    xs = [synth.text(n, 40 + i) for i, n in enumerate(sizes)]
+    arcs = [ax.encode(x, threads=8) for x in xs]
+    assert all(np.array_equal(oracle.decode(a), x) for a, x in zip(arcs, xs))
+    decs = [ax.Decoder(a, torch.from_numpy(a).cuda()) for a in arcs]
+    outs = [torch.full((x.size + 16,), 0xCC, dtype=torch.uint8, device="cuda") for x in xs]
+    batch = ax.Batch(decs, outs)
+    _say("finish of a batch", sizes)
+    batch.decode()
+    assert batch.status()[0] == 0
+    for x, o in zip(xs, outs):
+        _same(o.cpu().numpy(), x)
+
+
 def _fastest(dec, out, n=8):
     ms = []
     for _ in range(n):
