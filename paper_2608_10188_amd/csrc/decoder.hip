@@ -833,7 +833,10 @@ __device__ inline bool leb_staged(const uint8_t* src, const uint16_t* end, uint3
 // scan over the staged bytes lists where every value ends) and read by the
 // command that needs them, instead of a scan over a window of the stream for
 // every chunk: 64 KiB of DNA parse in 42 -> 29 us, 254 MB in 253 -> 208 us.
-template <class O, bool kRecs, uint32_t kT>
+//
+// kRecs: 0 no records, 1 records for the match layer, 2 also count the match
+// bytes of open blocks (as a branch of 1 it costs the smallest decodes 0.2 us).
+template <class O, int kRecs, uint32_t kT>
 __global__ __launch_bounds__(kT, kT == kParseThreads ? 7 : 4) void k_parse(ParseArgs a) {
   __shared__ ParseShared<kT> sh;
   const uint32_t item = blockIdx.x, t = threadIdx.x;
@@ -1082,7 +1085,7 @@ __global__ __launch_bounds__(kT, kT == kParseThreads ? 7 : 4) void k_parse(Parse
     return;
   }
   if (!kRecs) return;
-  if (item >= a.open0 && item < a.open1 && t < 64) {
+  if (kRecs == 2 && item >= a.open0 && item < a.open1 && t < 64) {
     // not those of a block that does little but repeat its own bytes: walks end there at once
     uint32_t from = 0;
     if (t < tok_n) {
@@ -2955,7 +2958,7 @@ constexpr uint32_t kFinishWords = 4;
 // reads (chains of long hops) measure the same with all of them.
 constexpr uint32_t kSweepBack = 4;
 constexpr uint32_t kFinishLimit = 1u << 24;  // hops k_finish follows before it reports a device error
-constexpr uint32_t kSweepLimit = 1u << 28;   // the same for a sweep: a run has at most so many positions, and a hop goes down
+constexpr uint32_t kSweepLimit = 1u << 24;   // hops after which a sweep leaves the rest of its walks to k_finish
 
 struct SweepArgs {
   uint32_t s_log2;
@@ -3036,7 +3039,7 @@ __device__ __forceinline__ void sweep_run(const SweepArgs& a, uint32_t block, ui
           v[u] = in[u] ? J[q.g[c + u] * 64 + lane] : kJRes;
           was[u] = v[u];
         }
-        for (uint32_t hop = 1;; ++hop) {
+        for (uint32_t hop = 1; hop < kSweepLimit; ++hop) {
           bool more = false;
 #pragma unroll
           for (uint32_t u = 0; u < kSweepRows; ++u)
@@ -3045,10 +3048,6 @@ __device__ __forceinline__ void sweep_run(const SweepArgs& a, uint32_t block, ui
           for (uint32_t u = 0; u < kSweepRows; ++u) more |= !(v[u] & kJRes) && v[u] >= lo;
           if (!__ballot(more)) break;
           if (hop % kSweepBack) continue;
-          if (hop >= kSweepLimit) {
-            if (lane == 0) report(a.st, AX_E_DEVICE, ~0ull);
-            return;
-          }
 #pragma unroll
           for (uint32_t u = 0; u < kSweepRows; ++u)
             if (v[u] != was[u]) J[q.g[c + u] * 64 + lane] = was[u] = v[u];
@@ -3064,7 +3063,7 @@ __device__ __forceinline__ void sweep_run(const SweepArgs& a, uint32_t block, ui
     uint32_t p[kSweepSlots], v[kSweepSlots], nx[kSweepSlots];  // byte (or none), where its walk is, next word
 #pragma unroll
     for (uint32_t u = 0; u < kSweepSlots; ++u) p[u] = ~0u, v[u] = 0, nx[u] = u;
-    for (uint32_t hop = 1;; ++hop) {
+    for (uint32_t hop = 1; hop < kSweepLimit; ++hop) {
       bool busy = false;
 #pragma unroll
       for (uint32_t u = 0; u < kSweepSlots; ++u) {
@@ -3075,10 +3074,6 @@ __device__ __forceinline__ void sweep_run(const SweepArgs& a, uint32_t block, ui
         busy |= p[u] != ~0u || nx[u] < cnt;
       }
       if (!__ballot(busy)) break;
-      if (hop >= kSweepLimit) {
-        if (lane == 0) report(a.st, AX_E_DEVICE, ~0ull);
-        return;
-      }
       uint32_t jn[kSweepSlots];
       uint64_t w[kSweepSlots];
 #pragma unroll
@@ -3744,7 +3739,7 @@ int plan_parse_tokens(Plan* P, void* d_work, uint64_t work_len, hipStream_t s, u
     ParseArgs pa{P->d_jobs, wbl, W.items, W.tok, P->slot_b, w + L.lit, w + L.cmd, w + L.off, w + L.len, P->off_cap,
                  P->len_cap, reinterpret_cast<const uint32_t*>(w + L.nsym), reinterpret_cast<uint64_t*>(w + L.tok),
                  nullptr, nullptr, st, 0};
-    hipLaunchKernelGGL((k_parse<OutDirect, false, kParseThreads>), dim3(W.items), dim3(kParseThreads), 0, s, pa);
+    hipLaunchKernelGGL((k_parse<OutDirect, 0, kParseThreads>), dim3(W.items), dim3(kParseThreads), 0, s, pa);
     try {
       tk.resize(2ull * W.tok);
     } catch (const std::bad_alloc&) {
@@ -4040,14 +4035,20 @@ static void enqueue_out(Plan* P, uint8_t* w, int copy_mode, hipStream_t s, bool 
                  P->len_cap, reinterpret_cast<const uint32_t*>(w + L.nsym), reinterpret_cast<uint64_t*>(w + L.tok),
                  roots ? nullptr : reinterpret_cast<uint32_t*>(w + L.tblk), w + L.done, st, 1,
                  W.sure, roots ? W.sure + W.open : W.sure, counts};
-    if (!recs)
-      hipLaunchKernelGGL((k_parse<O, false, kParseThreads>), dim3(W.items), dim3(kParseThreads), 0, s, pa);
-    else if (W.items <= kParseWideBlocks)
-      hipLaunchKernelGGL((k_parse<O, true, kParseWide>), dim3(W.items), dim3(kParseWide), 0, s, pa);
-    else if (W.items <= kParseMidBlocks)
-      hipLaunchKernelGGL((k_parse<O, true, kParseMid>), dim3(W.items), dim3(kParseMid), 0, s, pa);
-    else
-      hipLaunchKernelGGL((k_parse<O, true, kParseThreads>), dim3(W.items), dim3(kParseThreads), 0, s, pa);
+    auto parse = [&](auto recs_tag, auto threads_tag) {
+      constexpr uint32_t kT = decltype(threads_tag)::value;
+      hipLaunchKernelGGL((k_parse<O, decltype(recs_tag)::value, kT>), dim3(W.items), dim3(kT), 0, s, pa);
+    };
+    using Narrow = std::integral_constant<uint32_t, kParseThreads>;
+    using Mid = std::integral_constant<uint32_t, kParseMid>;
+    using Wide = std::integral_constant<uint32_t, kParseWide>;
+    const std::integral_constant<int, 1> records;
+    const std::integral_constant<int, 2> counted;
+    if (!recs) parse(std::integral_constant<int, 0>{}, Narrow{});
+    else if (roots && W.open) W.items <= kParseMidBlocks ? parse(counted, Mid{}) : parse(counted, Narrow{});
+    else if (W.items <= kParseWideBlocks) parse(records, Wide{});
+    else if (W.items <= kParseMidBlocks) parse(records, Mid{});
+    else parse(records, Narrow{});
     if (ev) (void)hipEventRecord(ev[2], s);
     if (roots) {
       if (ntok) enqueue_roots<O>(P, W, wbl, w, s, ev);
