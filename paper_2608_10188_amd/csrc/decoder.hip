@@ -21,7 +21,7 @@
 //     final after the parse; the bytes of long chains, and every byte of
 //     archives taken to be deep (k_mark), become entries of a jump array that
 //     k_sweep and k_finish resolve.
-//   - rounds (chosen by the schedule options, and for the serial ablation):
+//   - rounds (once one of their knobs is set, and for the serial ablation):
 //     the tokens whose destinations meet a token's source bytes form one
 //     contiguous index range (tokens are stored in output order), found once
 //     by binary search; a token is ready when those are done.  k_round0 (a
@@ -34,6 +34,10 @@
 //     k_pscatter compact into an ascending list for k_tail, one persistent
 //     launch whose waves take 64-token chunks from a ticket counter and publish
 //     through agent-coherent stores.
+//
+// Times that a comment sets against each other are whole decodes unless it says
+// otherwise, of two builds in one session on the code of their day; what else
+// changed since moves both sides.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -2439,9 +2443,9 @@ __global__ __launch_bounds__(kCopyThreads) void k_jgather(JumpArgs a) {
 // marks a final byte) and leftover map these kernels use.
 
 constexpr uint32_t kRootItem = 16;   // bytes per work item: one 16-byte source load
-// Steps before a walk's bytes are left pending (decode of 254 MB DNA / 32 MiB
-// reads with 3, 4, 6, 9 and 12 steps: 861 / 273, 816 / 265, 778 / 262, 765 /
-// 262, 792 / 279 us).
+// Steps before a walk's bytes are left pending (against nine, 254 MB of DNA / 32
+// MiB of reads take with 3, 4, 6 and 12 steps 1.13 / 1.04, 1.07 / 1.01, 1.02 / 1.00
+// and 1.04 / 1.07 times as long).
 constexpr uint32_t kRootSteps = 9;
 
 // The window's first blocks are marked, the others walked: those of archives
@@ -2820,9 +2824,8 @@ __device__ __forceinline__ void roots_block(const RootArgs& a, uint32_t first, u
 }
 
 // log2 of the positions a workgroup of k_mark takes: small in small windows,
-// where a workgroup's chain of loads is what counts (text 1 MB: 94 -> 91 us
-// for the decode with 1024 instead of 4096), large in others (text 80 MiB:
-// 783 -> 764 us with 4096)
+// where a workgroup's chain of loads is what counts (1 MB of text 3 % faster
+// with 1024 than with 4096), large in others (80 MiB of text 2 % faster with 4096)
 constexpr uint32_t kMarkSmallLog2 = 10, kMarkLog2 = 12;
 
 // Blocks of deep archives: walks would not end in a few steps, so every byte
@@ -2939,7 +2942,7 @@ constexpr uint32_t kXcds = 8;
 constexpr uint32_t kSweepSlots = 4;    // bytes a lane follows at a time
 constexpr uint32_t kSweepRows = 8;     // map words a wave follows at a time where every byte has an entry
 // Consecutive map words a wave takes at a time: rows of whole words where every
-// byte has an entry (80 MiB text with 8 / 4 / 2: 733 / 778 / 804 us), fewer
+// byte has an entry (80 MiB of text with 4 / 2: 1.06 / 1.10 times as long), fewer
 // where pending bytes come in clusters (with 4 / 2 / 1: 16 MiB of DNA in 4 KiB
 // blocks 151 / 145 / 145 us, 32 MiB of reads 226 / 222 / 223, 254 MB of DNA 685 /
 // 680 / 686).
@@ -3461,13 +3464,13 @@ static uint32_t jump_pass_bound(uint64_t tok) {
 // 441 and 373, 461 and 489, 518 and 1021; log lines with long random fields (53 %)
 // 481 and 985, zero pages among random ones (72 %) 416 and 540, text with matches of
 // 16 and more 425 and 672.  Asking costs 3 to 6 %.
-// In small plans the marking is cheap and its shorter
-// chain of loads counts: 64 KiB / 4 MiB DNA 94 / 122 us against 140 / 148 us.
-// Between 8 and 16 MiB it depends on the data: 12 MiB of DNA 121 us marked and
-// 136 walked, but 16 MiB of protein 120 and 104, 10 MiB of DNA in 4 KiB blocks
-// 140 and 115.
+// In small plans the marking is cheap and its shorter chain of loads counts: 64
+// KiB / 4 MiB of DNA 94 / 122 us marked and 140 / 148 walked.  Between 8 and 16 MiB
+// it depends on the data: 12 MiB of DNA 121 and 136, but 16 MiB of protein 120 and
+// 104, 10 MiB of DNA in 4 KiB blocks 140 and 115.
 constexpr uint64_t kDeepRatio = 3;
-constexpr uint64_t kDenseSpan = 256, kDenseMatch = 10, kOpenMatch = 20, kBlockOverhead = 64;  // bytes of a block that holds nothing
+constexpr uint64_t kDenseSpan = 256, kDenseMatch = 10, kOpenMatch = 20;
+constexpr uint64_t kBlockOverhead = 64;  // payload bytes of a block that holds nothing
 constexpr uint64_t kCopiedShare = 3;
 constexpr uint64_t kDeepSmall = 8u << 20;  // positions of a small plan
 // Marked blocks are finished run by run (eight launches, each reading settled
