@@ -77,4 +77,4 @@ def test_chains_of_short_hops(n, w, lit, timed):
     assert np.array_equal(out.cpu().numpy()[: x.size], x)
     ref = _fastest(rounds, out)
     _say("rows", n, w, lit, "ms", ms, "rounds", ref)
-    assert ms <= ref
+    assert ms <= 1.1 * ref  # runs of one build differ by a few percent
